@@ -1003,7 +1003,7 @@ std::string operand_loader(const KInfo& ki, const GemmSpec& sp, bool isA, const 
 // same chunk pair for all of them) on 16 distinct 16-byte bank groups of the
 // 256-byte bank cycle.  f may not use bit 2 of k: the two reads of one
 // fragment are 4 rows apart and share f.
-static bool dma_b_swizzle(int P, int& x0, int& x1, int& x3) {
+bool dma_b_swizzle(int P, int& x0, int& x1, int& x3) {
   static const int vals[] = {0, 2, 4, 6, 8, 10, 12, 14};
   for (int a : vals)
     for (int b : vals)
@@ -1033,7 +1033,7 @@ static bool dma_b_swizzle(int P, int& x0, int& x1, int& x3) {
   return false;
 }
 
-static std::string dma_fk(const GemmSpec& sp, const std::string& k) {
+std::string dma_fk(const GemmSpec& sp, const std::string& k) {
   std::string r;
   auto term = [&](int x, const std::string& bit) {
     if (!x) return;
@@ -1129,6 +1129,19 @@ static DmaRoles dma_roles(const GemmSpec& sp) {
   return r;
 }
 
+std::string operand_batch_offset(const KInfo& ki, const GemmSpec& sp, int node) {
+  const Shape& sh = ki.g.nodes[node].shape;
+  Shape ob(sp.OUT.begin(), sp.OUT.begin() + sp.nb);
+  Shape nbsh(sh.begin(), sh.end() - 2);
+  std::vector<Ix> zc;
+  for (int d = 0; d < sp.nb; ++d) zc.push_back(Ix::var("z" + std::to_string(d)));
+  auto bi = broadcast_index(nbsh, ob, zc);
+  auto st = strides_of(sh);
+  Ix off = Ix::k(0);
+  for (size_t d = 0; d < bi.size(); ++d) off = ix_add(off, ix_mulk(bi[d], st[d], 1));
+  return off.at();
+}
+
 // Per-wave load offsets and the staging lambdas `dmaA_(kt, st)` and
 // `dmaB_(kt, st)` (each called only by the waves that load that operand).
 static std::string dma_loader(const KInfo& ki, const GemmSpec& sp, const std::map<int, int>& slot) {
@@ -1137,18 +1150,7 @@ static std::string dma_loader(const KInfo& ki, const GemmSpec& sp, const std::ma
   const DmaRoles R = dma_roles(sp);
   const int P = sp.BN / 8;
   const int64_t SAE = (int64_t)sp.BM * 64, SBE = (int64_t)sp.BN * 64, BOFF = sp.dsa * SAE;
-  auto boff = [&](int node) {
-    const Shape& sh = g.nodes[node].shape;
-    Shape ob(sp.OUT.begin(), sp.OUT.begin() + sp.nb);
-    Shape nbsh(sh.begin(), sh.end() - 2);
-    std::vector<Ix> zc;
-    for (int d = 0; d < sp.nb; ++d) zc.push_back(Ix::var("z" + std::to_string(d)));
-    auto bi = broadcast_index(nbsh, ob, zc);
-    auto st = strides_of(sh);
-    Ix off = Ix::k(0);
-    for (size_t d = 0; d < bi.size(); ++d) off = ix_add(off, ix_mulk(bi[d], st[d], 1));
-    return off.at();
-  };
+  auto boff = [&](int node) { return operand_batch_offset(ki, sp, node); };
   std::ostringstream s;
   s << "  // direct-to-LDS staging: " << sp.BM / 8 << " A blocks and " << sp.BN / 8 << " B blocks of 1 KiB per k-tile, "
     << sp.dsa << " A stages and " << sp.dsb << " B stages\n";
@@ -1845,6 +1847,27 @@ static bool eight_wave_dma(const KInfo& ki, GemmSpec& sp, int64_t tiles, int64_t
   return true;
 }
 
+std::string gemm_tile_order(const GemmSpec& sp, int64_t ntm, int64_t ntn) {
+  // Workgroups are dispatched round-robin over the 8 XCDs, each with its own
+  // L2.  Renumber them so every XCD owns a contiguous range of tiles, and order
+  // tiles in groups of GM row-tiles so the tiles running together on one XCD
+  // share their A row-panels and B column-panels in that XCD's L2.
+  int64_t total = ntn * ntm * sp.batch;
+  std::ostringstream s;
+  int64_t GM = std::min<int64_t>(8, ntm);
+  s << "  const int wg = blockIdx.x, xcd = wg % 8, jx = wg / 8;\n";
+  s << "  const int q = xcd * " << total / 8 << " + (xcd < " << total % 8 << " ? xcd : " << total % 8 << ") + jx;\n";
+  s << "  const int bz_ = q / " << ntm * ntn << ", r_ = q % " << ntm * ntn << ";\n";
+  s << "  const int grp = r_ / " << GM * ntn << ", first = grp * " << GM << ";\n";
+  s << "  const int gs = " << ntm << " - first < " << GM << " ? " << ntm << " - first : " << GM << ";\n";
+  s << "  const int tm = first + (r_ % " << GM * ntn << ") % gs, tn = (r_ % " << GM * ntn << ") / gs;\n";
+  s << "  const i64 n0 = (i64)tn * " << sp.BN << ", m0 = (i64)tm * " << sp.BM << ";\n";
+  s << "  i64 q_ = bz_;\n";
+  for (int d = sp.nb - 1; d >= 0; --d)
+    s << "  const i64 z" << d << " = q_ % " << sp.OUT[d] << "LL; q_ /= " << sp.OUT[d] << "LL;\n";
+  return s.str();
+}
+
 GenKernel gen_gemm(const KInfo& ki, int index) {
   GemmSpec sp;
   std::string why;
@@ -1853,6 +1876,10 @@ GenKernel gen_gemm(const KInfo& ki, int index) {
   if (sp.conv && !sp.pro.empty()) fail(KORCH_E_UNSUPPORTED, "conv: a weight prologue needs the direct kernel");
   choose_tiles(sp, false);
   plan_operands(ki, sp);
+  {
+    const int64_t kt = (sp.K + sp.BK - 1) / sp.BK, tiles = (sp.M + sp.BM - 1) / sp.BM * ((sp.N + sp.BN - 1) / sp.BN) * sp.batch;
+    if (plan_phased(ki, sp, sp.mms.size() == 1 && sp.NT == 256 && tiles <= 256 && kt >= 16)) return gen_gemm_phased(ki, sp, index);
+  }
   if ((sp.K + sp.BK - 1) / sp.BK > 128) sp.NS = 2;  // long contractions use the rolled loop
   if (sp.WM > 1 && !getenv("KORCH_GEMM_FULL_CTILE")) sp.CROWS = sp.WTM;
   GenKernel gk;
@@ -1921,22 +1948,8 @@ GenKernel gen_gemm(const KInfo& ki, int index) {
     s << gemm_prologue_common(sp);
     if (sp.dma) s << "  char* gsm_ = smem;  // operand stages\n";
   }
-  // Workgroups are dispatched round-robin over the 8 XCDs, each with its own
-  // L2.  Renumber them so every XCD owns a contiguous range of tiles, and order
-  // tiles in groups of GM row-tiles so the tiles running together on one XCD
-  // share their A row-panels and B column-panels in that XCD's L2.
-  int64_t total = ntn * ntm * sp.batch;
-  int64_t GM = std::min<int64_t>(8, ntm);
-  s << "  const int wg = blockIdx.x, xcd = wg % 8, jx = wg / 8;\n";
-  s << "  const int q = xcd * " << total / 8 << " + (xcd < " << total % 8 << " ? xcd : " << total % 8 << ") + jx;\n";
-  s << "  const int bz_ = q / " << ntm * ntn << ", r_ = q % " << ntm * ntn << ";\n";
-  s << "  const int grp = r_ / " << GM * ntn << ", first = grp * " << GM << ";\n";
-  s << "  const int gs = " << ntm << " - first < " << GM << " ? " << ntm << " - first : " << GM << ";\n";
-  s << "  const int tm = first + (r_ % " << GM * ntn << ") % gs, tn = (r_ % " << GM * ntn << ") / gs;\n";
-  s << "  const i64 n0 = (i64)tn * " << sp.BN << ", m0 = (i64)tm * " << sp.BM << ";\n";
-  s << "  i64 q_ = bz_;\n";
-  for (int d = sp.nb - 1; d >= 0; --d)
-    s << "  const i64 z" << d << " = q_ % " << sp.OUT[d] << "LL; q_ /= " << sp.OUT[d] << "LL;\n";
+  const int64_t total = ntn * ntm * sp.batch;
+  s << gemm_tile_order(sp, ntm, ntn);
   if (ksplit)
     s << "  const int kt0 = kgrp * " << KH << ", kt1 = kt0 + " << KH << " < " << KT << " ? kt0 + " << KH << " : " << KT
       << ";\n";

@@ -1,0 +1,413 @@
+// Phased main loop of the GEMM family: plain 16-bit products staged direct to
+// LDS, one barrier per k-tile with the matrix cores busy across it.
+//
+// What bounds it: of a 16384 x 1024 x 4096 product with 256 x 256 tiles (109 us,
+// 1.26 PFLOP/s; the 128 x 128 tiles staged as before took 195 us) the loads
+// alone take 101 us and the products with their LDS reads alone 72, so the tile
+// is as large as registers and LDS allow and the loads run under the products;
+// the L2 misses are the compulsory ones, and each compute unit's L1 is refused
+// requests 56 % of the time for having about 80 in flight.  LDS reads cost
+// nothing measurable: two wave rows of 128 tile rows each read the right operand,
+// whose transposing reads are the slow ones, only twice.
+//
+// A k-tile is NP phases: its k-steps, and the wave's row blocks in pairs.  Phase
+// p multiplies fragments that were read one or two phases before, and the barrier
+// that hands a tile over stands before the LAST phases: by then every wave holds
+// their fragments in registers, so the stage is free, the next loads are issued
+// into it at once, and the last phases' MFMAs cover the barrier and the first
+// fragment reads of the next tile.
+#include <algorithm>
+#include <cstdio>
+#include <cstdlib>
+
+#include "families.h"
+#include "gemm_common.h"
+
+namespace korch {
+
+static bool env_set(const char* n) {
+  const char* e = getenv(n);
+  return e && *e;
+}
+
+// Tile shape, waves, k-groups and stages of the phased path; false: not taken.
+//
+// Each shape's cost on a product is predicted from the k-tile (64) times it
+// reached when the chip was full of it (measured on products of 128 to 16384
+// rows, contractions of 128 to 4096): t1 us with one workgroup per compute
+// unit, tc us with the c that fit there at once (their k-tiles together), and
+// ov us per round of workgroups for the first loads and the epilogue.  The last,
+// partial round pays for the workgroups it puts on one compute unit.  Large
+// tiles draw the fewest operand bytes per product, which is what bounds a full
+// chip: each compute unit's L1 holds about 80 outstanding 128-byte requests of
+// some 620 clocks (at 256 x 256 it is refused requests 56 % of the time; L2
+// misses are the compulsory ones); small tiles with deep stages cover latency
+// when there are few of them.
+static bool phased_tiles(GemmSpec& sp) {
+  if (const char* e = getenv("KORCH_GEMM_PHASED")) {
+    int bm, bn, wm, wn, kg, st, bk;
+    if (sscanf(e, "%d,%d,%d,%d,%d,%d,%d", &bm, &bn, &wm, &wn, &kg, &bk, &st) != 7) return false;
+    sp.BM = bm, sp.BN = bn, sp.WM = wm, sp.WN = wn, sp.KG = kg, sp.PST = st, sp.BK = bk;
+    return true;
+  }
+  struct Shape_ {
+    int bm, bn, wm, wn, kg, st, c;
+    double t1, tc, ov;
+  };
+  static const Shape_ shapes[] = {
+      {256, 256, 2, 4, 1, 2, 1, 1.50, 1.50, 9.5}, {256, 128, 2, 4, 1, 3, 1, 0.87, 0.87, 4.9}, {128, 128, 2, 2, 1, 2, 2, 0.62, 1.00, 3.2},
+      {128, 128, 2, 4, 1, 4, 1, 0.50, 0.50, 2.6}, {128, 96, 2, 2, 1, 2, 2, 0.60, 0.88, 2.8},  {128, 96, 4, 2, 1, 5, 1, 0.46, 0.46, 2.2},
+      {128, 64, 4, 2, 1, 5, 1, 0.31, 0.31, 2.2},  {128, 64, 2, 2, 1, 3, 2, 0.31, 0.57, 2.4},  {64, 128, 2, 2, 1, 3, 2, 0.31, 0.56, 2.3},
+      {64, 64, 2, 2, 1, 4, 2, 0.22, 0.38, 1.7},   {32, 64, 2, 2, 1, 6, 2, 0.17, 0.29, 1.6},   {32, 64, 2, 2, 2, 6, 1, 0.155, 0.155, 1.6},
+  };
+  const double KT = (double)((sp.K + 63) / 64);
+  double best = 1e300;
+  for (const Shape_& h : shapes) {
+    const int64_t tiles = (sp.M + h.bm - 1) / h.bm * ((sp.N + h.bn - 1) / h.bn) * sp.batch;
+    const int64_t full = tiles / (256 * h.c), rest = (tiles - full * 256 * h.c + 255) / 256;
+    // two k-groups halve a workgroup's chain of k-tiles: for few tiles only
+    if (h.kg > 1 && (tiles > 64 || KT < 16)) continue;
+    const double tr = h.c > 1 ? h.t1 + (h.tc - h.t1) * (double)(rest - 1) / (h.c - 1) : h.t1;
+    const double cost = full * (KT * h.tc + h.ov) + (rest ? KT * tr + h.ov : 0.0);
+    if (cost < best) {
+      best = cost;
+      sp.BM = h.bm, sp.BN = h.bn, sp.WM = h.wm, sp.WN = h.wn, sp.KG = h.kg, sp.PST = h.st, sp.BK = 64;
+    }
+  }
+  return true;
+}
+
+// Row blocks per band of the fp32 C tile (a divisor of FM): at most four
+// 16-byte output vectors per thread and band, and two bands in LDS.
+static int phased_band(const GemmSpec& sp) {
+  for (int f : {4, 2})
+    if (sp.FM % f == 0 && sp.WM * 16 * f * sp.BN <= 32 * sp.NT && (size_t)2 * sp.WM * 16 * f * sp.LDC * 4 <= 160 * 1024) return f;
+  return 1;
+}
+
+static size_t phased_smem(const GemmSpec& sp) {
+  const size_t st = (size_t)sp.PST * sp.KG * (sp.BM + sp.BN) * sp.BK * 2;
+  if (sp.acc_t) return std::max(st, (size_t)sp.OSB);
+  return std::max(st, sp.KG > 1 ? (size_t)sp.BM * sp.LDC * 4 : (size_t)2 * sp.WM * 16 * phased_band(sp) * sp.LDC * 4);
+}
+
+bool plan_phased(const KInfo& ki, GemmSpec& sp, bool split_halves) {
+  sp.KG = 0;
+  // the switches of the older staging paths ask for those paths
+  for (const char* n : {"KORCH_GEMM_CFG", "KORCH_GEMM_NS", "KORCH_GEMM_NO_KSPLIT", "KORCH_GEMM_DMA", "KORCH_GEMM_DMA8",
+                        "KORCH_GEMM_DMA_KSPLIT", "KORCH_GEMM_DMA_2STAGE", "KORCH_GEMM_DMA_A3", "KORCH_GEMM_DMA_STAGES",
+                        "KORCH_GEMM_SPLIT_STEPS"})
+    if (env_set(n)) return false;
+  if (sp.conv || sp.lnf || sp.mms.size() != 1 || sp.Bs.size() != 1 || !sp.b_kn) return false;
+  if (sp.mtype != KORCH_F16 && sp.mtype != KORCH_BF16) return false;
+  if (ki.in.count(sp.A) || ki.in.count(sp.Bs[0])) return false;  // operands computed in the kernel
+  if (sp.K % 8 || sp.N % 8) return false;                        // 16-byte chunks of rows
+  // buffer loads: byte offsets below 2 GiB from a batch's operand
+  if ((double)sp.M * sp.K * 2 >= 2147483648.0 || (double)sp.K * sp.N * 2 >= 2147483648.0) return false;
+  // Products that 192-wide tiles divide into whole rounds keep those tiles and
+  // their own staging (4096 x 3072 x 768 with a GELU: 22.9 us, phased 22.4).
+  if (!getenv("KORCH_GEMM_PHASED") && sp.BN == 192) return false;
+  // So do small products of up to four k-tiles whose tiles divide them: there is
+  // nothing to pipeline (1024 x 768 x 256: 3.8 us, phased 3.9; 16384 x 64 x 256:
+  // 3.7 either way; 4096 x 1024 x 256, above the line: 6.7 and 6.0).
+  if (!getenv("KORCH_GEMM_PHASED") && sp.M * sp.N * sp.batch <= 1 << 20 && sp.K <= 256 && sp.K % 64 == 0 && sp.M % sp.BM == 0 &&
+      sp.N % sp.BN == 0)
+    return false;
+  GemmSpec t = sp;
+  if (!phased_tiles(t)) return false;
+  // A long contraction whose 128-row tiles leave at most one per compute unit
+  // is summed in two halves that are added at the end, as its k-split kernel
+  // with register staging does: the results are the same to the bit (wave tiles
+  // of up to 16 blocks, which leave registers for the second set of sums).
+  t.KSEQ = t.KG == 1 && split_halves && t.BM / t.WM * (t.BN / t.WN) <= 16 * 256 ? 2 : 1;
+  if (t.WM < 1 || t.WN < 1 || t.KG < 1 || t.BM % (16 * t.WM) || t.BN % (16 * t.WN)) return false;
+  const int gw = t.WM * t.WN;  // waves per group
+  t.NT = 64 * gw * t.KG;
+  if (t.NT != 256 && t.NT != 512) return false;
+  if (t.BK != 32 && t.BK != 64) return false;
+  if ((t.BM * t.BK / 512) % gw || t.BN * t.BK % 512) return false;  // whole blocks, the left operand's shared evenly
+  t.WTM = t.BM / t.WM, t.WTN = t.BN / t.WN;
+  t.FM = t.WTM / 16, t.FN = t.WTN / 16;
+  if (t.PST < 2 || t.PST > 12) return false;
+  t.LDC = t.BN + 4;
+  if (!dma_b_swizzle(t.BN / 8, t.dx0, t.dx1, t.dx3)) return false;
+  t.acc_t = false;
+  t.OSP = t.OSB = 0;
+  t.CROWS = 0;
+  if (t.KG == 1 && reg_epilogue_output(ki, t) >= 0) {
+    t.acc_t = true;
+    t.OSP = t.BN + 8;
+    t.OSB = t.BM * t.OSP * 2;
+  }
+  if (phased_smem(t) > 160 * 1024) return false;
+  sp = t;
+  return true;
+}
+
+
+// Operand loads.  A block is 1 KiB: of the left operand 8 rows of 64 k, row r's
+// 16-byte chunk c at position c ^ (r & 7) (k-tiles of 32: 16 rows, c ^ 2 (r / 4
+// mod 2)), so that the lanes of a fragment read that the LDS serves together
+// fall on 16 distinct bank groups; of the right operand 64 consecutive chunks of
+// the [k][BN] tile, row k's chunk c at c ^ f(k) (dma_b_swizzle).
+// Buffer loads, so rows and columns past the problem are clamped to its last
+// ones (their products are never stored) and, where 64 does not divide K, the
+// last k-tile's missing chunks read zero (an offset past the buffer).  M0 holds
+// the LDS address; the wait state between its write and the load that reads it
+// is spelled out, since the compiler does not see into the statement.
+static std::string phased_loader(const KInfo& ki, const GemmSpec& sp, const std::map<int, int>& slot) {
+  const std::string T = ctype(sp.mtype);
+  const int GW = sp.WM * sp.WN, PA = sp.BM * sp.BK / 512 / GW, NB = sp.BN * sp.BK / 512, PB = (NB + GW - 1) / GW, P = sp.BN / 8;
+  const int64_t SAE = (int64_t)sp.BM * sp.BK, SBE = (int64_t)sp.BN * sp.BK;  // elements of a stage
+  const int64_t KT = (sp.K + sp.BK - 1) / sp.BK;
+  const int CR = sp.BK / 8, RB = 64 / CR;  // chunks per left row, rows per block
+  std::ostringstream s;
+  s << "  const int wv_ = __builtin_amdgcn_readfirstlane(wave);\n";
+  s << "  const unsigned lds0_ = (unsigned)(size_t)(__attribute__((address_space(3))) void*)gsm_;\n";
+  s << "  typedef int i32x4_ __attribute__((ext_vector_type(4)));\n";
+  auto rsrc = [&](const char* X, int node, int64_t bytes) {
+    s << "  const size_t p" << X << "_ = (size_t)((const " << T << "*)a.p[" << slot.at(node) << "] + ("
+      << operand_batch_offset(ki, sp, node) << "));\n";
+    s << "  const i32x4_ rs" << X << "_ = {__builtin_amdgcn_readfirstlane((int)(unsigned)p" << X
+      << "_), __builtin_amdgcn_readfirstlane((int)((p" << X << "_ >> 32) & 0xffff)), " << (long long)bytes << ", 0x00020000};\n";
+  };
+  rsrc("A", sp.A, sp.M * sp.K * 2);
+  rsrc("B", sp.Bs[0], sp.K * sp.N * 2);
+  // k of this lane's left chunk within a tile (its position holds chunk c ^ g(row))
+  s << "  const int lk_ = " << (sp.BK == 64 ? "((l & 7) ^ (l >> 3)) * 8" : "((l & 3) ^ ((l >> 3) & 2)) * 8") << ";\n";
+  s << "  unsigned va_[" << PA << "], vb_[" << PB << "];  // byte offsets of this lane's chunks at k-tile 0\n";
+  s << "#pragma unroll\n  for (int i = 0; i < " << PA << "; ++i) {\n";
+  s << "    i64 r = m0 + " << RB << " * (wv_ + i * " << GW << ") + l / " << CR << ";\n";
+  if (sp.M % sp.BM) s << "    r = r < " << sp.M << "LL ? r : " << sp.M - 1 << "LL;\n";
+  s << "    va_[i] = (unsigned)((r * " << sp.K << "LL + lk_) * 2);\n  }\n";
+  s << "#pragma unroll\n  for (int i = 0; i < " << PB << "; ++i) {\n";
+  s << "    const int q = (wv_ + i * " << GW << ") * 64 + l, k = q / " << P << ", p = q % " << P << ";\n";
+  s << "    i64 c = n0 + ((p ^ " << dma_fk(sp, "k") << ") * 8);\n";
+  if (sp.N % sp.BN) s << "    c = c < " << sp.N << "LL ? c : " << sp.N - 8 << "LL;\n";
+  s << "    vb_[i] = (unsigned)(((i64)k * " << sp.N << "LL + c) * 2);\n  }\n";
+  auto ld = [&](const char* off, const char* rs) {
+    return std::string("      asm volatile(\"s_mov_b32 m0, %1\\n\\ts_nop 0\\n\\tbuffer_load_dwordx4 %0, %2, %3 offen lds\" :: \"v\"(") +
+           off + "), \"s\"(la), \"s\"(" + rs + "), \"s\"(so) : \"memory\", \"m0\");\n";
+  };
+  const bool tail = sp.K % sp.BK != 0;
+  // tile kt into stage st
+  s << "  auto load_ = [&](const int kt, const int st) {\n";
+  s << "    {\n    const unsigned so = (unsigned)kt * " << sp.BK * 2 << "u;\n#pragma unroll\n    for (int i = 0; i < " << PA << "; ++i) {\n";
+  s << "      const unsigned la = lds0_ + (unsigned)((st * " << SAE << " + (wv_ + i * " << GW << ") * 512) * 2);\n";
+  if (tail)
+    s << "      const unsigned vo = kt == " << KT - 1 << " && lk_ >= " << sp.K % sp.BK
+      << " ? 0x80000000u : va_[i];\n"
+      << ld("vo", "rsA_");
+  else
+    s << ld("va_[i]", "rsA_");
+  s << "    }\n    }\n";
+  s << "    {\n    const unsigned so = (unsigned)kt * " << 2 * sp.BK * sp.N << "u;\n#pragma unroll\n    for (int i = 0; i < " << PB << "; ++i) {\n";
+  if (NB % GW) s << "      if (i == " << PB - 1 << " && wv_ >= " << NB % GW << ") break;  // the first waves load one block more\n";
+  s << "      const unsigned la = lds0_ + (unsigned)((" << sp.PST * SAE << " + st * " << SBE << " + (wv_ + i * " << GW << ") * 512) * 2);\n";
+  if (tail)
+    s << "      const unsigned vo = kt == " << KT - 1 << " && ((wv_ + i * " << GW << ") * 64 + l) / " << P << " >= " << sp.K % sp.BK
+      << " ? 0x80000000u : vb_[i];\n"
+      << ld("vo", "rsB_");
+  else
+    s << ld("vb_[i]", "rsB_");
+  s << "    }\n    }\n  };\n";
+  return s.str();
+}
+
+static std::string phased_mainloop(const GemmSpec& sp, int64_t KTG, bool exact) {
+  std::ostringstream s;
+  const std::string T = ctype(sp.mtype), V8 = sp.mtype == KORCH_F16 ? "f16x8" : "bf16x8";
+  const std::string fn = sp.mtype == KORCH_F16 ? "__builtin_amdgcn_mfma_f32_16x16x32_f16"
+                                               : "__builtin_amdgcn_mfma_f32_16x16x32_bf16";
+  const int FH = sp.FM % 2 ? 1 : 2, H = sp.FM / FH, nkk = sp.BK / 32, NP = nkk * H;  // row blocks per phase; phases
+  const int L = std::min(2, H), NA = 2 * L;  // phases a left fragment is read ahead; register sets
+  const int NST = sp.PST, GW = sp.WM * sp.WN, PL = (sp.BM + sp.BN) * sp.BK / 512 / GW;  // loads per wave and tile
+  const int PX = (sp.BN * sp.BK / 512) % GW;  // waves with one load more
+  // tiles per round: stages, left register sets and right register sets repeat
+  int U = NST;
+  while ((U * NP) % NA || (U * nkk) % 2) U += NST;
+  // all stages of the left operand, then all of the right one: with 64 KiB or
+  // less of each, a fragment's address is a lane's base plus an immediate
+  const int64_t SAE = (int64_t)sp.BM * sp.BK, SBE = (int64_t)sp.BN * sp.BK;
+  s << "  f32x4 acc[" << sp.FM << "][" << sp.FN << "];\n";
+  s << "#pragma unroll\n  for (int i = 0; i < " << sp.FM << "; ++i)\n#pragma unroll\n  for (int j = 0; j < " << sp.FN
+    << "; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};\n";
+  s << "  " << V8 << " fa_[" << NA << "][" << FH << "], fb_[2][" << sp.FN << "];\n";
+  s << "  const " << T << "* Af_ = (const " << T << "*)gsm_ + (wm * " << sp.WTM << " + (l & 15)) * " << sp.BK << ";\n";
+  s << "  const int ca_ = " << (sp.BK == 64 ? "((l >> 4) ^ (l & 7)) * 8" : "((l >> 4) ^ ((l >> 1) & 2)) * 8") << ";\n";
+  s << "  const " << T << "* Bf_ = (const " << T << "*)gsm_ + " << NST * SAE << " + ((l >> 4) * 8 + ((l & 15) >> 2)) * " << sp.BN << ";\n";
+  s << "  int cb_[" << sp.FN << "];\n#pragma unroll\n  for (int j = 0; j < " << sp.FN << "; ++j) {\n";
+  s << "    const int n_ = wn * " << sp.WTN << " + j * 16 + 4 * (l & 3), k_ = (l >> 4) * 8 + ((l & 15) >> 2);\n";
+  s << "    cb_[j] = (((n_ >> 3) ^ " << dma_fk(sp, "k_") << ") * 8) + (n_ & 7);\n  }\n";
+  // left fragments of phase p (rows [p % H * FH, + FH), k-step p / H) of tile t
+  // (counted within a round), right fragment j of its k-step kk
+  auto setA = [&](int t, int p) { return ((t % U) * NP + p) % NA; };
+  auto setB = [&](int t, int kk) { return ((t % U) * nkk + kk) % 2; };
+  auto readA = [&](int t, int p) {
+    std::ostringstream o;
+    for (int i = 0; i < FH; ++i)
+      o << "    fa_[" << setA(t, p) << "][" << i << "] = *(const " << V8 << "*)(Af_ + "
+        << (t % NST) * SAE + ((p % H) * FH + i) * 16 * sp.BK << " + (ca_ ^ " << (p / H) * 32 << "));\n";
+    return o.str();
+  };
+  auto readB = [&](int t, int kk, int j) {
+    std::ostringstream o;
+    o << "    fb_[" << setB(t, kk) << "][" << j << "] = __builtin_bit_cast(" << V8 << ", lds_tr_k8(Bf_ + "
+      << (t % NST) * SBE + kk * 32 * sp.BN << " + cb_[" << j << "], " << sp.BN << "));\n";
+    return o.str();
+  };
+  // right fragments [FN h / parts, FN (h + 1) / parts)
+  auto readBs = [&](int t, int kk, int h, int parts) {
+    std::string o;
+    for (int j = sp.FN * h / parts; j < sp.FN * (h + 1) / parts; ++j) o += readB(t, kk, j);
+    return o;
+  };
+  // waits until at most the loads of n tiles are in flight
+  auto wait = [&](int n) {
+    auto w = [](int c) { return "asm volatile(\"s_waitcnt vmcnt(" + std::to_string(c) + ")\" ::: \"memory\");\n"; };
+    if (!n || !PX) return "    " + w(n * PL);
+    return "    if (wv_ < " + std::to_string(PX) + ") " + w(n * (PL + 1)) + "    else " + w(n * PL);
+  };
+  // Tile j of the group, number t of a round.  `more`: tile j + NST exists (1)
+  // or may exist (2); `next`: tile j + 1 exists; `steady`: tiles j + 2 .. j +
+  // NST - 1 exist in every group and are the loads in flight beyond tile j + 1;
+  // `live`: the group may have no tile j (a shorter last group).
+  auto tile = [&](const std::string& j, int t, int more, bool next, bool steady, bool live) {
+    std::ostringstream o;
+    for (int p = 0; p < NP; ++p) {
+      if (p == NP - L && next) {
+        // tile j + 1 has landed and every wave holds the rest of tile j
+        o << wait(steady ? NST - 2 : 0) << "    __syncthreads();\n";
+        if (more)
+          o << (more == 2 ? "    if (" + j + " + " + std::to_string(NST) + " < nkt_) " : std::string("    ")) << "load_(kt0 + " << j
+            << " + " << NST << ", " << t % NST << ");\n";
+      }
+      const int q = p + L;
+      if (q < NP) o << readA(t, q);
+      else if (next) o << readA(t + 1, q - NP);
+      for (int kk = 1; kk < nkk; ++kk)
+        if (p / H == kk - 1) o << readBs(t, kk, p % H, H);
+      if (p >= NP - L && next) o << readBs(t + 1, 0, p - (NP - L), L);
+      o << (live ? "    if (" + j + " < nkt_) {\n" : "    {\n");
+      const int h = p % H;
+      for (int i = 0; i < FH; ++i)
+        for (int n = 0; n < sp.FN; ++n) {
+          const std::string A = "fa_[" + std::to_string(setA(t, p)) + "][" + std::to_string(i) + "]",
+                            B = "fb_[" + std::to_string(setB(t, p / H)) + "][" + std::to_string(n) + "]",
+                            C = "acc[" + std::to_string(h * FH + i) + "][" + std::to_string(n) + "]";
+          o << "      " << C << " = " << fn << "(" << (sp.acc_t ? B + ", " + A : A + ", " + B) << ", " << C << ", 0, 0, 0);\n";
+        }
+      o << "    }\n    __builtin_amdgcn_sched_barrier(0);\n";
+    }
+    if (sp.KSEQ > 1) {
+      // the end of the first half: its sums are set aside
+      o << "    if (" << j << " == " << (KTG + 1) / 2 - 1 << ") {\n#pragma unroll\n      for (int i = 0; i < " << sp.FM
+        << "; ++i)\n#pragma unroll\n        for (int n = 0; n < " << sp.FN
+        << "; ++n) { acc0_[i][n] = acc[i][n]; acc[i][n] = f32x4{0.0f, 0.0f, 0.0f, 0.0f}; }\n    }\n";
+    }
+    return o.str();
+  };
+  if (sp.KSEQ > 1) s << "  f32x4 acc0_[" << sp.FM << "][" << sp.FN << "];  // kgrp 0: the sums of the first half of the k-tiles\n";
+  s << "  const int nkt_ = kt1 - kt0;\n  (void)nkt_;\n";
+  const int64_t KS = exact ? KTG : KTG - 1;  // k-tiles that every group has
+  for (int t = 0; t < NST && t < KTG; ++t)
+    s << "  " << (t < KS ? "" : "if (" + std::to_string(t) + " < nkt_) ") << "load_(kt0 + " << t << ", " << t << ");\n";
+  // tile 0 landed; the tiles after it may be in flight
+  s << wait(KS >= NST ? NST - 1 : 0) << "  __syncthreads();\n";
+  for (int p = 0; p < L; ++p) s << readA(0, p);
+  s << readBs(0, 0, 0, 1);
+  // steady part: tile j + NST exists in every group, in rounds of U tiles
+  const int64_t steady = KS > NST ? (KS - NST) / U * U : 0;
+  if (steady > 0) {
+    s << "#pragma unroll 1\n  for (int j = 0; j < " << steady << "; j += " << U << ") {\n";
+    for (int u = 0; u < U; ++u) s << tile("(j + " + std::to_string(u) + ")", u, 1, true, true, false);
+    s << "  }\n";
+  }
+  for (int64_t j = steady; j < KTG; ++j) {
+    const int more = j + NST < KS ? 1 : j + NST < KTG ? 2 : 0;
+    s << "  {\n" << tile(std::to_string(j), (int)(j % U), more, j + 1 < KTG, j + NST - 1 < KS, j >= KS) << "  }\n";
+  }
+  if (sp.KSEQ > 1)
+    s << "#pragma unroll\n  for (int i = 0; i < " << sp.FM << "; ++i)\n#pragma unroll\n  for (int n = 0; n < " << sp.FN
+      << "; ++n) acc[i][n] = acc0_[i][n] + acc[i][n];\n";
+  s << "  __syncthreads();\n";
+  return s.str();
+}
+
+GenKernel gen_gemm_phased(const KInfo& ki, GemmSpec& sp, int index) {
+  GenKernel gk;
+  gk.family = KORCH_FAM_GEMM;
+  gk.name = kernel_name(index, "gemm");
+  std::map<int, int> slot;
+  ki.assign_args(gk, slot);
+  const int64_t ntn = (sp.N + sp.BN - 1) / sp.BN, ntm = (sp.M + sp.BM - 1) / sp.BM, KT = (sp.K + sp.BK - 1) / sp.BK;
+  const int64_t KTG = (KT + sp.KG - 1) / sp.KG;  // k-tiles of a group
+  const std::string T = ctype(sp.mtype);
+  const int GT = 64 * sp.WM * sp.WN;  // threads of a group
+  std::ostringstream s;
+  s << source_header((int)gk.args.size());
+  s << "extern \"C\" __global__ void __launch_bounds__(" << sp.NT << ") __attribute__((amdgpu_waves_per_eu(2))) " << gk.name << "(KArgs a) {\n";
+  s << "  __shared__ __attribute__((aligned(1024))) char smem[" << phased_smem(sp) << "];\n";
+  if (sp.KG > 1) {
+    s << "  const int kgrp = __builtin_amdgcn_readfirstlane(threadIdx.x / " << GT << ");  // which part of the k-tiles\n";
+    s << "  char* gsm_ = smem + kgrp * " << sp.PST * (sp.BM + sp.BN) * sp.BK * 2 << ";  // this group's operand stages\n";
+    s << "  const int tid = threadIdx.x % " << GT << ", l = tid & 63, wave = tid >> 6;\n";
+  } else {
+    s << "  char* gsm_ = smem;  // operand stages\n";
+    s << "  const int tid = threadIdx.x, l = tid & 63, wave = tid >> 6;\n";
+  }
+  s << "  const int wm = wave / " << sp.WN << ", wn = wave % " << sp.WN << ";\n  (void)wm; (void)wn;\n";
+  s << gemm_tile_order(sp, ntm, ntn);
+  if (sp.KG > 1)
+    s << "  const int kt0 = kgrp * " << KTG << ", kt1 = kt0 + " << KTG << " < " << KT << " ? kt0 + " << KTG << " : " << KT << ";\n";
+  else
+    s << "  const int kt0 = 0, kt1 = " << KT << ";\n";
+  s << phased_loader(ki, sp, slot);
+  s << phased_mainloop(sp, KTG, KT % sp.KG == 0);
+  auto ctile = [&](const char* op) {
+    std::ostringstream o;
+    o << "#pragma unroll\n    for (int i = 0; i < " << sp.FM << "; ++i)\n#pragma unroll\n    for (int j = 0; j < " << sp.FN
+      << "; ++j)\n#pragma unroll\n    for (int r = 0; r < 4; ++r) Cs[((" << (sp.KG > 1 ? "wm * " + std::to_string(sp.WTM) : std::string("0"))
+      << ") + i * 16 + (l >> 4) * 4 + r) * " << sp.LDC << " + wn * " << sp.WTN << " + j * 16 + (l & 15)] " << op << " acc[i][j][r];\n";
+    return o.str();
+  };
+  // The epilogue's lane indices go through an opaque copy: its many LDS and
+  // output addresses would otherwise be computed ahead of the main loop and
+  // held (spilled) across it.
+  s << "  int te_ = threadIdx.x;\n  asm volatile(\"\" : \"+v\"(te_));\n  {\n  const int tid = te_"
+    << (sp.KG > 1 ? " % " + std::to_string(GT) : std::string()) << ", l = tid & 63, wave = tid >> 6, wm = wave / " << sp.WN
+    << ", wn = wave % " << sp.WN << ";\n  (void)wm; (void)wn;\n";
+  if (sp.acc_t) {
+    s << gemm_reg_epilogue(ki, sp, slot, reg_epilogue_output(ki, sp));
+  } else if (sp.KG > 1) {
+    // the groups' sums one after another in group order
+    s << "  float* Cs = (float*)smem;\n";
+    for (int q = 0; q < sp.KG; ++q) s << "  if (kgrp == " << q << ") {\n" << ctile(q ? "+=" : "=") << "  }\n  __syncthreads();\n";
+    s << "  {\n  const int tid = te_;\n";
+    s << gemm_epilogue(ki, sp, slot, "ml * " + std::to_string(sp.LDC));
+    s << "  }\n";
+  } else {
+    // The fp32 C tile in NQ bands, each FQ row blocks of every wave row, through
+    // two LDS buffers: a band is evaluated and stored while the accumulators of
+    // the later ones are still in registers, with one barrier per band.
+    const int FQ = phased_band(sp), NQ = sp.FM / FQ, R = 16 * FQ, rows = sp.WM * R;
+    s << "  float* Cs = (float*)smem;\n";
+    for (int q = 0; q < NQ; ++q) {
+      s << "  {\n#pragma unroll\n  for (int i = 0; i < " << FQ << "; ++i)\n#pragma unroll\n  for (int j = 0; j < " << sp.FN
+        << "; ++j)\n#pragma unroll\n  for (int r = 0; r < 4; ++r) Cs[(" << (q & 1) * rows << " + wm * " << R
+        << " + i * 16 + (l >> 4) * 4 + r) * " << sp.LDC << " + wn * " << sp.WTN << " + j * 16 + (l & 15)] = acc[" << q * FQ
+        << " + i][j][r];\n  }\n  __syncthreads();\n";
+      s << gemm_epilogue(ki, sp, slot, "(" + std::to_string((q & 1) * rows) + " + mlc) * " + std::to_string(sp.LDC), {}, 0, rows,
+                         "(mlc / " + std::to_string(R) + ") * " + std::to_string(sp.WTM - R) + " + " + std::to_string(q * R));
+    }
+  }
+  s << "  }\n}\n";
+  gk.source = s.str();
+  gk.grid[0] = (int)(ntn * ntm * sp.batch);
+  gk.block[0] = sp.NT;
+  gk.lds_bytes = (int)phased_smem(sp);
+  ki.fill_cost(gk);
+  return gk;
+}
+
+}  // namespace korch

@@ -67,6 +67,11 @@ struct GemmSpec {
   int dsb = 2;  // right-operand stages
   int dsa = 2;  // left-operand stages (3: loaded two k-tiles ahead like the right operand)
   bool want_a3 = false;  // ask plan_dma for three left-operand stages
+  // Phased main loop (fam_gemm_phased.cpp): groups of WM x WN waves, each over
+  // its own part of the k-tiles (0: not taken).
+  int KG = 0;
+  int PST = 2;   // its stages of each operand
+  int KSEQ = 1;  // parts of the contraction summed one after another, then added
   // LayerNorm folded into the product (see detect_ln_fold): the left operand
   // is LN(X) = (X - mu) r gamma + beta over X's last axis; the kernel stages X,
   // multiplies X gamma by the right operand W, accumulates each row's sum and
@@ -82,6 +87,19 @@ struct GemmSpec {
 
 // Decides direct-to-LDS staging (sets sp.dma) once tiles and the epilogue are known.
 void plan_dma(const KInfo& ki, GemmSpec& sp, bool ksplit);
+
+// XOR masks of the right operand's chunk index in a direct-to-LDS stage with P
+// chunks per row, and the expression f(k) they define (fam_gemm.cpp).
+bool dma_b_swizzle(int P, int& x0, int& x1, int& x3);
+std::string dma_fk(const GemmSpec& sp, const std::string& k);
+// Element offset of the batch (z0, z1, ...) in a product operand.
+std::string operand_batch_offset(const KInfo& ki, const GemmSpec& sp, int node);
+// Definitions of the workgroup's batch coordinates and tile origin (m0, n0).
+std::string gemm_tile_order(const GemmSpec& sp, int64_t ntm, int64_t ntn);
+// Phased main loop: decides (tiles, waves, k-groups) and generates.
+// split_halves: the older path would split the contraction in two inside a workgroup.
+bool plan_phased(const KInfo& ki, GemmSpec& sp, bool split_halves);
+GenKernel gen_gemm_phased(const KInfo& ki, GemmSpec& sp, int index);
 
 // LDS element offset of row k of the [k][n] right-operand tile.
 std::string b_row_off(const GemmSpec& sp, const std::string& k);

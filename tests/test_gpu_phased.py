@@ -1,0 +1,159 @@
+"""The GEMM family's phased main loop (direct-to-LDS tiles, one barrier per
+k-tile inside the products) against float64 products.
+
+Every tile shape of its rule, and forms beyond it (k-tiles of 32, k-groups),
+on sizes that leave partial tiles in every direction: rows, columns (multiples
+of 8, as the path takes), contractions that 64 or 32 do not divide, fewer
+k-tiles than stages, odd numbers of them, batches with a shared right operand.
+The bound per element is the output's rounding plus the fp32 accumulation of K
+products, K 2^-24 sum |a b| (each of the K additions rounds to 24 bits).
+"""
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+SHAPES = ["256,256,2,4,1,64,2", "256,128,2,4,1,64,3", "128,128,2,2,1,64,2", "128,128,2,4,1,64,4", "128,96,2,2,1,64,2",
+          "128,96,4,2,1,64,5", "128,64,4,2,1,64,5", "128,64,2,2,1,64,3", "64,128,2,2,1,64,3", "64,64,2,2,1,64,4",
+          "32,64,2,2,1,64,6", "32,64,2,2,2,64,6", "256,256,2,4,1,32,5", "128,96,2,2,2,32,5"]
+SIZES = [(300, 264, 200), (1, 8, 8), (257, 520, 64), (128, 96, 1000), (33, 72, 456)]
+
+
+def _graph(m, n, k, dtype, epi, batch=0):
+    from paper_2406_09465_amd._abi import Graph
+    from paper_2406_09465_amd.graphs import Workload
+    g = Graph()
+    lead = (batch,) if batch else ()
+    ids = {"A": g.input(dtype, lead + (m, k)), "W": g.input(dtype, (k, n))}
+    names = ["A", "W"]
+    if epi == "residual":
+        ids["R"] = g.input(dtype, lead + (m, n))
+        names.append("R")
+    if batch:  # a right operand shared by the batch
+        ids["Wb"] = g.op("reshape", [ids["W"]], dtype, shape=(1, k, n))
+    ids["C"] = g.op("matmul", [ids["A"], ids["Wb" if batch else "W"]], dtype)
+    ids["out"] = ids["C"]
+    prims = ([ids["Wb"]] if batch else []) + [ids["C"]]
+    if epi == "residual":
+        ids["out"] = g.op("add", [ids["C"], ids["R"]], dtype)
+        prims.append(ids["out"])
+    g.output(ids["out"])
+    g.finalize()
+    return Workload("product", dtype, g, ids, names, ["out"]), [([p for p in prims if p != ids.get("Wb")], [ids["out"]])]
+
+
+def _run(m, n, k, dtype, epi, batch=0, edit=None, seed=0):
+    from paper_2406_09465_amd.runner import TORCH_DTYPE, PlanRunner
+    w, kernels = _graph(m, n, k, dtype, epi, batch)
+    r = PlanRunner(w, kernels=kernels)
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    lead = (batch,) if batch else ()
+    shapes = {"A": lead + (m, k), "W": (k, n), "R": lead + (m, n)}
+    x = {nm: torch.randn(shapes[nm], generator=gen, device="cuda").to(TORCH_DTYPE[dtype]) for nm in w.input_names}
+    if edit:
+        edit(x)
+    r.ins = [x[nm] for nm in w.input_names]
+    r.bind()
+    r.launch_bound()
+    torch.cuda.synchronize()
+    return r, {nm: v.double().cpu() for nm, v in x.items()}
+
+
+def _check(r, x, k, dtype):
+    out = r.outs[0].double().cpu()
+    ref = x["A"] @ x["W"]
+    mag = x["A"].abs() @ x["W"].abs()
+    if "R" in x:
+        ref = ref + x["R"]
+        mag = mag + x["R"].abs()
+    eps = 2.0 ** -11 if dtype == "f16" else 2.0 ** -8
+    bound = eps * ref.abs() * 1.01 + (k + 2) * 2.0 ** -24 * mag + 2.0 ** -24
+    bad = (out - ref).abs() > bound
+    assert not bool(bad.any()), f"{int(bad.sum())} of {bad.numel()} beyond the bound, worst {float(((out - ref).abs() / bound).max()):.2f}"
+
+
+@pytest.mark.parametrize("cfg", SHAPES)
+def test_phased_kernels_compile_without_spills(cfg, monkeypatch):
+    """Each tile shape with a plain store and with a residual epilogue."""
+    from paper_2406_09465_amd import codeobj
+    from paper_2406_09465_amd._abi import Plan
+    monkeypatch.setenv("KORCH_GEMM_PHASED", cfg)
+    bm, bn, wm, wn, kg, bk, st = map(int, cfg.split(","))
+    for epi in ("", "residual"):
+        w, kernels = _graph(700, 520, 1032, "bf16", epi)
+        p = Plan(w.graph, kernels)
+        p.compile()
+        (grid, block, lds) = p.kernel_launch(0)
+        assert grid[0] == -(-700 // bm) * -(-520 // bn) and block[0] == 64 * wm * wn * kg and lds <= 160 * 1024
+        assert "offen lds" in p.kernel_source(0)
+        (res,) = codeobj.kernel_resources(p.kernel_code(0)).values()
+        assert res["scratch"] == 0 and res["vgpr"] + res["agpr"] <= 512 // (block[0] // 256)
+
+
+def test_phased_selection():
+    """Plain 16-bit products take the path; fp32 ones, operands computed in the
+    kernel, rows that are not 16-byte chunks and small short products do not."""
+    from paper_2406_09465_amd._abi import Plan
+
+    def phased(m, n, k, dtype):
+        w, kernels = _graph(m, n, k, dtype, "")
+        p = Plan(w.graph, kernels)
+        return "offen lds" in p.kernel_source(0)
+
+    assert phased(4096, 1024, 1024, "bf16") and phased(1576, 384, 1536, "f16") and phased(301, 264, 1000, "f16")
+    assert not phased(4096, 1024, 1024, "f32") and not phased(4096, 1024, 1020, "f16") and not phased(512, 512, 128, "f16")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("size", SIZES, ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("cfg", SHAPES)
+def test_phased_product(cfg, size, monkeypatch):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    monkeypatch.setenv("KORCH_GEMM_PHASED", cfg)
+    m, n, k = size
+    for dtype, epi, batch in (("f16", "", 0), ("bf16", "residual", 0), ("f16", "residual", 3)):
+        print(f"\n[case] phased {cfg} {size} {dtype} {epi} batch {batch}", flush=True)
+        r, x = _run(m, n, k, dtype, epi, batch, seed=m + n + k)
+        assert "offen lds" in r.plan.kernel_source(0)
+        _check(r, x, k, dtype)
+        first = r.outs[0].clone()
+        for _ in range(5):
+            r.launch_bound()
+        torch.cuda.synchronize()
+        assert torch.equal(first.view(torch.int16), r.outs[0].view(torch.int16))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("size", [(4096, 1024, 1024), (2048, 768, 3072), (1000, 1000, 1000), (64, 512, 4096), (5000, 96, 264)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_phased_default_choice(size):
+    """The shapes the rule takes by itself (long contractions in two halves among them)."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    m, n, k = size
+    print(f"\n[case] phased default {size}", flush=True)
+    r, x = _run(m, n, k, "f16", "residual", seed=5)
+    assert "offen lds" in r.plan.kernel_source(0)
+    _check(r, x, k, "f16")
+
+
+@pytest.mark.gpu
+def test_phased_nonfinite_rows_stay_apart():
+    """A contraction that 64 does not divide: the chunks past a row's end are
+    the next row's, and must not reach this row's sums even when they are
+    infinite or NaN."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+    def edit(x):
+        x["A"][1::2] = float("inf")
+        x["A"][3::4, 7] = float("nan")
+
+    print("\n[case] phased nonfinite", flush=True)
+    r, x = _run(130, 136, 1000, "f16", "", edit=edit)
+    out = r.outs[0].double().cpu()
+    ref = x["A"][0::2] @ x["W"]
+    assert bool(torch.isfinite(out[0::2]).all()) and np.allclose(out[0::2], ref, rtol=2e-3, atol=0.15)
+    assert not bool(torch.isfinite(out[1::2]).any())
