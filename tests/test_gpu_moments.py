@@ -110,3 +110,30 @@ def test_moments_repeats_bitwise():
         r.launch()
         torch.cuda.synchronize()
         assert all(torch.equal(a.view(torch.int16), b.view(torch.int16)) for a, b in zip(first, r.outs)), f"execution {i}"
+
+
+# Row batches and splits of the column moments: one workgroup of four and of
+# eight waves, the smallest split (one row over what one workgroup takes), a
+# last split of a few rows, several batches of a thread's rows, more partials
+# than one batch of the last workgroup's loads, odd channel counts.
+@pytest.mark.parametrize("dtype", ["f32", "f16"])
+@pytest.mark.parametrize("hh,ww,c", [(3, 5, 32), (32, 32, 32), (41, 25, 32), (61, 67, 24), (7, 130, 6), (449, 451, 32), (300, 301, 128),
+                                     (129, 127, 3)])
+def test_moments_row_batches(hh, ww, c, dtype):
+    from paper_2406_09465_amd import graphs
+    from paper_2406_09465_amd.runner import PlanRunner
+    print(f"\n[case] moments rows {hh}x{ww}x{c} {dtype}", flush=True)
+    sizes = dict(hh=hh, ww=ww, c=c, dtype=dtype)
+    w, _ = graphs.rewritten(graphs.build("instnorm", **sizes))
+    raw, x = inputs_f64("instnorm", **sizes)
+    r = PlanRunner(w, kernels=graphs.moments_plan(w))
+    out = r.run(raw)["out"]
+    d = x["X"] - x["X"].mean((0, 1))
+    y = d / np.sqrt((d * d).mean((0, 1)) + 1e-5) * x["gamma"] + x["beta"]
+    ref = np.pad(np.maximum(y, 0), ((1, 1), (1, 1), (0, 0)))
+    ok, mx, rel = close(out, ref, TOL[dtype])
+    assert ok, f"max abs err {mx:.3e}, normwise rel {rel:.3e}"
+    first = [t.clone() for t in r.outs]
+    r.launch()
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(first, r.outs))
