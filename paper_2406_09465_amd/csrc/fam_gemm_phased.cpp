@@ -54,6 +54,32 @@ static bool phased_tiles(GemmSpec& sp) {
     int bm, bn, wm, wn, kg, st, c;
     double t1, tc, ov;
   };
+  double best = 1e300;
+  if (sp.mtype == KORCH_F32) {
+    // fp32 products are bound by their MFMAs (16x16x4: a quarter of a 16-bit
+    // k-step's products in twice the clocks), so what a tile costs is its area
+    // and how evenly the tiles fall on the compute units: t1 us per k-tile (32)
+    // when a compute unit has one tile (its waves wait alone), tc us per tile
+    // when it has several.  2048 x 3072 x 768: 64 x 96 tiles 74.9 us (128 x 96
+    // staged through registers 83.4); 2048 x 768 x 3072: 73.4 in two k-groups
+    // (92.5); 340 x 256 x 1024: 32 x 32 tiles 6.9 (64 x 64: 23.2).
+    static const Shape_ f32s[] = {
+        {64, 128, 2, 2, 1, 2, 0, 1.14, 0.97, 4.0},  {64, 96, 2, 2, 1, 2, 0, 0.80, 0.745, 3.5}, {64, 64, 2, 2, 1, 2, 0, 0.62, 0.475, 3.0},
+        {32, 64, 2, 2, 1, 4, 0, 0.32, 0.25, 2.5},   {32, 32, 2, 2, 1, 4, 0, 0.172, 0.13, 1.8}, {64, 96, 2, 2, 2, 3, 0, 0.75, 0.75, 3.0},
+        {32, 64, 2, 2, 2, 6, 0, 0.285, 0.285, 2.0}, {32, 32, 2, 2, 2, 6, 0, 0.15, 0.15, 1.6},
+    };
+    const double KT = (double)((sp.K + 31) / 32);
+    for (const Shape_& h : f32s) {
+      const int64_t tiles = (sp.M + h.bm - 1) / h.bm * ((sp.N + h.bn - 1) / h.bn) * sp.batch, n = (tiles + 255) / 256;
+      if (h.kg > 1 && (n > 1 || KT < 16)) continue;  // two k-groups share the compute unit of one tile
+      const double cost = h.ov + KT * (n == 1 ? h.t1 : n * h.tc);
+      if (cost < best) {
+        best = cost;
+        sp.BM = h.bm, sp.BN = h.bn, sp.WM = h.wm, sp.WN = h.wn, sp.KG = h.kg, sp.PST = h.st, sp.BK = 32;
+      }
+    }
+    return true;
+  }
   static const Shape_ shapes[] = {
       {256, 256, 2, 4, 1, 2, 1, 1.50, 1.50, 9.5}, {256, 128, 2, 4, 1, 3, 1, 0.87, 0.87, 4.9}, {128, 128, 2, 2, 1, 2, 2, 0.62, 1.00, 3.2},
       {128, 128, 2, 4, 1, 4, 1, 0.50, 0.50, 2.6}, {128, 96, 2, 2, 1, 2, 2, 0.60, 0.88, 2.8},  {128, 96, 4, 2, 1, 5, 1, 0.46, 0.46, 2.2},
@@ -61,7 +87,6 @@ static bool phased_tiles(GemmSpec& sp) {
       {64, 64, 2, 2, 1, 4, 2, 0.22, 0.38, 1.7},   {32, 64, 2, 2, 1, 6, 2, 0.17, 0.29, 1.6},   {32, 64, 2, 2, 2, 6, 1, 0.155, 0.155, 1.6},
   };
   const double KT = (double)((sp.K + 63) / 64);
-  double best = 1e300;
   for (const Shape_& h : shapes) {
     const int64_t tiles = (sp.M + h.bm - 1) / h.bm * ((sp.N + h.bn - 1) / h.bn) * sp.batch;
     const int64_t full = tiles / (256 * h.c), rest = (tiles - full * 256 * h.c + 255) / 256;
@@ -81,12 +106,12 @@ static bool phased_tiles(GemmSpec& sp) {
 // 16-byte output vectors per thread and band, and two bands in LDS.
 static int phased_band(const GemmSpec& sp) {
   for (int f : {4, 2})
-    if (sp.FM % f == 0 && sp.WM * 16 * f * sp.BN <= 32 * sp.NT && (size_t)2 * sp.WM * 16 * f * sp.LDC * 4 <= 160 * 1024) return f;
+    if (sp.FM % f == 0 && sp.WM * 16 * f * sp.BN <= 64 / dtype_bytes(sp.mtype) * sp.NT && (size_t)2 * sp.WM * 16 * f * sp.LDC * 4 <= 160 * 1024) return f;
   return 1;
 }
 
 static size_t phased_smem(const GemmSpec& sp) {
-  const size_t st = (size_t)sp.PST * sp.KG * (sp.BM + sp.BN) * sp.BK * 2;
+  const size_t st = (size_t)sp.PST * sp.KG * (sp.BM + sp.BN) * sp.BK * dtype_bytes(sp.mtype);
   if (sp.acc_t) return std::max(st, (size_t)sp.OSB);
   return std::max(st, sp.KG > 1 ? (size_t)sp.BM * sp.LDC * 4 : (size_t)2 * sp.WM * 16 * phased_band(sp) * sp.LDC * 4);
 }
@@ -99,11 +124,11 @@ bool plan_phased(const KInfo& ki, GemmSpec& sp, bool split_halves) {
                         "KORCH_GEMM_SPLIT_STEPS"})
     if (env_set(n)) return false;
   if (sp.conv || sp.lnf || sp.mms.size() != 1 || sp.Bs.size() != 1 || !sp.b_kn) return false;
-  if (sp.mtype != KORCH_F16 && sp.mtype != KORCH_BF16) return false;
+  const int eb = dtype_bytes(sp.mtype), CE = 16 / eb;
   if (ki.in.count(sp.A) || ki.in.count(sp.Bs[0])) return false;  // operands computed in the kernel
-  if (sp.K % 8 || sp.N % 8) return false;                        // 16-byte chunks of rows
+  if (sp.K % CE || sp.N % CE) return false;                      // 16-byte chunks of rows
   // buffer loads: byte offsets below 2 GiB from a batch's operand
-  if ((double)sp.M * sp.K * 2 >= 2147483648.0 || (double)sp.K * sp.N * 2 >= 2147483648.0) return false;
+  if ((double)sp.M * sp.K * eb >= 2147483648.0 || (double)sp.K * sp.N * eb >= 2147483648.0) return false;
   // Products that 192-wide tiles divide into whole rounds keep those tiles and
   // their own staging (4096 x 3072 x 768 with a GELU: 22.9 us, phased 22.4).
   if (!getenv("KORCH_GEMM_PHASED") && sp.BN == 192) return false;
@@ -124,13 +149,13 @@ bool plan_phased(const KInfo& ki, GemmSpec& sp, bool split_halves) {
   const int gw = t.WM * t.WN;  // waves per group
   t.NT = 64 * gw * t.KG;
   if (t.NT != 256 && t.NT != 512) return false;
-  if (t.BK != 32 && t.BK != 64) return false;
-  if ((t.BM * t.BK / 512) % gw || t.BN * t.BK % 512) return false;  // whole blocks, the left operand's shared evenly
+  if (t.BK != 4 * CE && t.BK != 8 * CE) return false;  // rows of 64 or 128 bytes
+  if ((t.BM * t.BK / (64 * CE)) % gw || t.BN * t.BK % (64 * CE)) return false;  // whole blocks, the left operand's shared evenly
   t.WTM = t.BM / t.WM, t.WTN = t.BN / t.WN;
   t.FM = t.WTM / 16, t.FN = t.WTN / 16;
   if (t.PST < 2 || t.PST > 12) return false;
   t.LDC = t.BN + 4;
-  if (!dma_b_swizzle(t.BN / 8, t.dx0, t.dx1, t.dx3)) return false;
+  if (CE == 8 && !dma_b_swizzle(t.BN / 8, t.dx0, t.dx1, t.dx3)) return false;
   t.acc_t = false;
   t.OSP = t.OSB = 0;
   t.CROWS = 0;
@@ -145,6 +170,17 @@ bool plan_phased(const KInfo& ki, GemmSpec& sp, bool split_halves) {
 }
 
 
+// Chunk of right row `k` that position `p` holds (load), or position of chunk
+// `p` (read).  16-bit rows: p ^ f(k).  fp32 rows turn by four chunks per four
+// rows: the four rows a fragment read takes at once (4 g + s, g = 0 .. 3) then
+// start on different 64-byte parts of the banks.
+static std::string b_chunk(const GemmSpec& sp, const std::string& p, const std::string& k, bool load) {
+  if (sp.mtype != KORCH_F32) return "((" + p + ") ^ " + dma_fk(sp, k) + ")";
+  const int P = sp.BN / 4;
+  const std::string rot = "(4 * (((" + k + ") >> 2) & 3)) % " + std::to_string(P);
+  return "(((" + p + ") + " + (load ? std::to_string(P) + " - " + rot : rot) + ") % " + std::to_string(P) + ")";
+}
+
 // Operand loads.  A block is 1 KiB: of the left operand 8 rows of 64 k, row r's
 // 16-byte chunk c at position c ^ (r & 7) (k-tiles of 32: 16 rows, c ^ 2 (r / 4
 // mod 2)), so that the lanes of a fragment read that the LDS serves together
@@ -157,10 +193,12 @@ bool plan_phased(const KInfo& ki, GemmSpec& sp, bool split_halves) {
 // is spelled out, since the compiler does not see into the statement.
 static std::string phased_loader(const KInfo& ki, const GemmSpec& sp, const std::map<int, int>& slot) {
   const std::string T = ctype(sp.mtype);
-  const int GW = sp.WM * sp.WN, PA = sp.BM * sp.BK / 512 / GW, NB = sp.BN * sp.BK / 512, PB = (NB + GW - 1) / GW, P = sp.BN / 8;
-  const int64_t SAE = (int64_t)sp.BM * sp.BK, SBE = (int64_t)sp.BN * sp.BK;  // elements of a stage
+  const int eb = dtype_bytes(sp.mtype), CE = 16 / eb;  // element bytes, elements per chunk
+  const int GW = sp.WM * sp.WN, PA = sp.BM * sp.BK / (64 * CE) / GW, NB = sp.BN * sp.BK / (64 * CE), PB = (NB + GW - 1) / GW;
+  const int P = sp.BN / CE;                                                    // chunks per right row
+  const int64_t SAB = (int64_t)sp.BM * sp.BK * eb, SBB = (int64_t)sp.BN * sp.BK * eb;  // bytes of a stage
   const int64_t KT = (sp.K + sp.BK - 1) / sp.BK;
-  const int CR = sp.BK / 8, RB = 64 / CR;  // chunks per left row, rows per block
+  const int CR = sp.BK / CE, RB = 64 / CR;  // chunks per left row, rows per block
   std::ostringstream s;
   s << "  const int wv_ = __builtin_amdgcn_readfirstlane(wave);\n";
   s << "  const unsigned lds0_ = (unsigned)(size_t)(__attribute__((address_space(3))) void*)gsm_;\n";
@@ -171,20 +209,20 @@ static std::string phased_loader(const KInfo& ki, const GemmSpec& sp, const std:
     s << "  const i32x4_ rs" << X << "_ = {__builtin_amdgcn_readfirstlane((int)(unsigned)p" << X
       << "_), __builtin_amdgcn_readfirstlane((int)((p" << X << "_ >> 32) & 0xffff)), " << (long long)bytes << ", 0x00020000};\n";
   };
-  rsrc("A", sp.A, sp.M * sp.K * 2);
-  rsrc("B", sp.Bs[0], sp.K * sp.N * 2);
+  rsrc("A", sp.A, sp.M * sp.K * eb);
+  rsrc("B", sp.Bs[0], sp.K * sp.N * eb);
   // k of this lane's left chunk within a tile (its position holds chunk c ^ g(row))
-  s << "  const int lk_ = " << (sp.BK == 64 ? "((l & 7) ^ (l >> 3)) * 8" : "((l & 3) ^ ((l >> 3) & 2)) * 8") << ";\n";
+  s << "  const int lk_ = " << (CR == 8 ? "((l & 7) ^ (l >> 3)) * " : "((l & 3) ^ ((l >> 3) & 2)) * ") << CE << ";\n";
   s << "  unsigned va_[" << PA << "], vb_[" << PB << "];  // byte offsets of this lane's chunks at k-tile 0\n";
   s << "#pragma unroll\n  for (int i = 0; i < " << PA << "; ++i) {\n";
   s << "    i64 r = m0 + " << RB << " * (wv_ + i * " << GW << ") + l / " << CR << ";\n";
   if (sp.M % sp.BM) s << "    r = r < " << sp.M << "LL ? r : " << sp.M - 1 << "LL;\n";
-  s << "    va_[i] = (unsigned)((r * " << sp.K << "LL + lk_) * 2);\n  }\n";
+  s << "    va_[i] = (unsigned)((r * " << sp.K << "LL + lk_) * " << eb << ");\n  }\n";
   s << "#pragma unroll\n  for (int i = 0; i < " << PB << "; ++i) {\n";
   s << "    const int q = (wv_ + i * " << GW << ") * 64 + l, k = q / " << P << ", p = q % " << P << ";\n";
-  s << "    i64 c = n0 + ((p ^ " << dma_fk(sp, "k") << ") * 8);\n";
-  if (sp.N % sp.BN) s << "    c = c < " << sp.N << "LL ? c : " << sp.N - 8 << "LL;\n";
-  s << "    vb_[i] = (unsigned)(((i64)k * " << sp.N << "LL + c) * 2);\n  }\n";
+  s << "    i64 c = n0 + " << b_chunk(sp, "p", "k", true) << " * " << CE << ";\n";
+  if (sp.N % sp.BN) s << "    c = c < " << sp.N << "LL ? c : " << sp.N - CE << "LL;\n";
+  s << "    vb_[i] = (unsigned)(((i64)k * " << sp.N << "LL + c) * " << eb << ");\n  }\n";
   auto ld = [&](const char* off, const char* rs) {
     return std::string("      asm volatile(\"s_mov_b32 m0, %1\\n\\ts_nop 0\\n\\tbuffer_load_dwordx4 %0, %2, %3 offen lds\" :: \"v\"(") +
            off + "), \"s\"(la), \"s\"(" + rs + "), \"s\"(so) : \"memory\", \"m0\");\n";
@@ -192,8 +230,8 @@ static std::string phased_loader(const KInfo& ki, const GemmSpec& sp, const std:
   const bool tail = sp.K % sp.BK != 0;
   // tile kt into stage st
   s << "  auto load_ = [&](const int kt, const int st) {\n";
-  s << "    {\n    const unsigned so = (unsigned)kt * " << sp.BK * 2 << "u;\n#pragma unroll\n    for (int i = 0; i < " << PA << "; ++i) {\n";
-  s << "      const unsigned la = lds0_ + (unsigned)((st * " << SAE << " + (wv_ + i * " << GW << ") * 512) * 2);\n";
+  s << "    {\n    const unsigned so = (unsigned)kt * " << sp.BK * eb << "u;\n#pragma unroll\n    for (int i = 0; i < " << PA << "; ++i) {\n";
+  s << "      const unsigned la = lds0_ + (unsigned)(st * " << SAB << " + (wv_ + i * " << GW << ") * 1024);\n";
   if (tail)
     s << "      const unsigned vo = kt == " << KT - 1 << " && lk_ >= " << sp.K % sp.BK
       << " ? 0x80000000u : va_[i];\n"
@@ -201,9 +239,9 @@ static std::string phased_loader(const KInfo& ki, const GemmSpec& sp, const std:
   else
     s << ld("va_[i]", "rsA_");
   s << "    }\n    }\n";
-  s << "    {\n    const unsigned so = (unsigned)kt * " << 2 * sp.BK * sp.N << "u;\n#pragma unroll\n    for (int i = 0; i < " << PB << "; ++i) {\n";
+  s << "    {\n    const unsigned so = (unsigned)kt * " << eb * sp.BK * sp.N << "u;\n#pragma unroll\n    for (int i = 0; i < " << PB << "; ++i) {\n";
   if (NB % GW) s << "      if (i == " << PB - 1 << " && wv_ >= " << NB % GW << ") break;  // the first waves load one block more\n";
-  s << "      const unsigned la = lds0_ + (unsigned)((" << sp.PST * SAE << " + st * " << SBE << " + (wv_ + i * " << GW << ") * 512) * 2);\n";
+  s << "      const unsigned la = lds0_ + (unsigned)(" << sp.PST * SAB << " + st * " << SBB << " + (wv_ + i * " << GW << ") * 1024);\n";
   if (tail)
     s << "      const unsigned vo = kt == " << KT - 1 << " && ((wv_ + i * " << GW << ") * 64 + l) / " << P << " >= " << sp.K % sp.BK
       << " ? 0x80000000u : vb_[i];\n"
@@ -216,13 +254,15 @@ static std::string phased_loader(const KInfo& ki, const GemmSpec& sp, const std:
 
 static std::string phased_mainloop(const GemmSpec& sp, int64_t KTG, bool exact) {
   std::ostringstream s;
-  const std::string T = ctype(sp.mtype), V8 = sp.mtype == KORCH_F16 ? "f16x8" : "bf16x8";
+  const std::string T = ctype(sp.mtype), V8 = sp.mtype == KORCH_F32 ? "f32x4" : sp.mtype == KORCH_F16 ? "f16x8" : "bf16x8";
+  const bool f32 = sp.mtype == KORCH_F32;
+  const int eb = dtype_bytes(sp.mtype), CE = 16 / eb, KW = 4 * CE;  // k of one fragment read (four chunks)
   const std::string fn = sp.mtype == KORCH_F16 ? "__builtin_amdgcn_mfma_f32_16x16x32_f16"
                                                : "__builtin_amdgcn_mfma_f32_16x16x32_bf16";
-  const int FH = sp.FM % 2 ? 1 : 2, H = sp.FM / FH, nkk = sp.BK / 32, NP = nkk * H;  // row blocks per phase; phases
+  const int FH = sp.FM % 2 ? 1 : 2, H = sp.FM / FH, nkk = sp.BK / KW, NP = nkk * H;  // row blocks per phase; phases
   const int L = std::min(2, H), NA = 2 * L;  // phases a left fragment is read ahead; register sets
-  const int NST = sp.PST, GW = sp.WM * sp.WN, PL = (sp.BM + sp.BN) * sp.BK / 512 / GW;  // loads per wave and tile
-  const int PX = (sp.BN * sp.BK / 512) % GW;  // waves with one load more
+  const int NST = sp.PST, GW = sp.WM * sp.WN, PL = (sp.BM + sp.BN) * sp.BK / (64 * CE) / GW;  // loads per wave and tile
+  const int PX = (sp.BN * sp.BK / (64 * CE)) % GW;  // waves with one load more
   // tiles per round: stages, left register sets and right register sets repeat
   int U = NST;
   while ((U * NP) % NA || (U * nkk) % 2) U += NST;
@@ -234,11 +274,14 @@ static std::string phased_mainloop(const GemmSpec& sp, int64_t KTG, bool exact) 
     << "; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};\n";
   s << "  " << V8 << " fa_[" << NA << "][" << FH << "], fb_[2][" << sp.FN << "];\n";
   s << "  const " << T << "* Af_ = (const " << T << "*)gsm_ + (wm * " << sp.WTM << " + (l & 15)) * " << sp.BK << ";\n";
-  s << "  const int ca_ = " << (sp.BK == 64 ? "((l >> 4) ^ (l & 7)) * 8" : "((l >> 4) ^ ((l >> 1) & 2)) * 8") << ";\n";
-  s << "  const " << T << "* Bf_ = (const " << T << "*)gsm_ + " << NST * SAE << " + ((l >> 4) * 8 + ((l & 15) >> 2)) * " << sp.BN << ";\n";
+  s << "  const int ca_ = " << (sp.BK / CE == 8 ? "((l >> 4) ^ (l & 7)) * " : "((l >> 4) ^ ((l >> 1) & 2)) * ") << CE << ";\n";
+  s << "  const " << T << "* Bf_ = (const " << T << "*)gsm_ + " << NST * SAE << " + (" << (f32 ? "(l >> 4) * 4" : "(l >> 4) * 8 + ((l & 15) >> 2)") << ") * " << sp.BN << ";\n";
   s << "  int cb_[" << sp.FN << "];\n#pragma unroll\n  for (int j = 0; j < " << sp.FN << "; ++j) {\n";
-  s << "    const int n_ = wn * " << sp.WTN << " + j * 16 + 4 * (l & 3), k_ = (l >> 4) * 8 + ((l & 15) >> 2);\n";
-  s << "    cb_[j] = (((n_ >> 3) ^ " << dma_fk(sp, "k_") << ") * 8) + (n_ & 7);\n  }\n";
+  if (f32)
+    s << "    const int n_ = wn * " << sp.WTN << " + j * 16 + (l & 15), k_ = (l >> 4) * 4;\n";
+  else
+    s << "    const int n_ = wn * " << sp.WTN << " + j * 16 + 4 * (l & 3), k_ = (l >> 4) * 8 + ((l & 15) >> 2);\n";
+  s << "    cb_[j] = " << b_chunk(sp, "n_ / " + std::to_string(CE), "k_", false) << " * " << CE << " + n_ % " << CE << ";\n  }\n";
   // left fragments of phase p (rows [p % H * FH, + FH), k-step p / H) of tile t
   // (counted within a round), right fragment j of its k-step kk
   auto setA = [&](int t, int p) { return ((t % U) * NP + p) % NA; };
@@ -247,13 +290,21 @@ static std::string phased_mainloop(const GemmSpec& sp, int64_t KTG, bool exact) 
     std::ostringstream o;
     for (int i = 0; i < FH; ++i)
       o << "    fa_[" << setA(t, p) << "][" << i << "] = *(const " << V8 << "*)(Af_ + "
-        << (t % NST) * SAE + ((p % H) * FH + i) * 16 * sp.BK << " + (ca_ ^ " << (p / H) * 32 << "));\n";
+        << (t % NST) * SAE + ((p % H) * FH + i) * 16 * sp.BK << " + (ca_ ^ " << (p / H) * 4 * CE << "));\n";
     return o.str();
   };
   auto readB = [&](int t, int kk, int j) {
     std::ostringstream o;
+    if (f32) {
+      // the contraction's order is free as long as both fragments agree: lane
+      // group g holds the consecutive k 4 g .. 4 g + 3 of the window (one
+      // 16-byte read of the left operand), and product s takes their s-th
+      o << "    {\n      const float* b_ = Bf_ + " << (t % NST) * SBE + kk * KW * sp.BN << " + cb_[" << j << "];\n      fb_[" << setB(t, kk)
+        << "][" << j << "] = f32x4{b_[0], b_[" << sp.BN << "], b_[" << 2 * sp.BN << "], b_[" << 3 * sp.BN << "]};\n    }\n";
+      return o.str();
+    }
     o << "    fb_[" << setB(t, kk) << "][" << j << "] = __builtin_bit_cast(" << V8 << ", lds_tr_k8(Bf_ + "
-      << (t % NST) * SBE + kk * 32 * sp.BN << " + cb_[" << j << "], " << sp.BN << "));\n";
+      << (t % NST) * SBE + kk * KW * sp.BN << " + cb_[" << j << "], " << sp.BN << "));\n";
     return o.str();
   };
   // right fragments [FN h / parts, FN (h + 1) / parts)
@@ -295,6 +346,12 @@ static std::string phased_mainloop(const GemmSpec& sp, int64_t KTG, bool exact) 
           const std::string A = "fa_[" + std::to_string(setA(t, p)) + "][" + std::to_string(i) + "]",
                             B = "fb_[" + std::to_string(setB(t, p / H)) + "][" + std::to_string(n) + "]",
                             C = "acc[" + std::to_string(h * FH + i) + "][" + std::to_string(n) + "]";
+          if (f32) {
+            for (int q = 0; q < 4; ++q)
+              o << "      " << C << " = __builtin_amdgcn_mfma_f32_16x16x4f32(" << A << "[" << q << "], " << B << "[" << q << "], " << C
+                << ", 0, 0, 0);\n";
+            continue;
+          }
           o << "      " << C << " = " << fn << "(" << (sp.acc_t ? B + ", " + A : A + ", " + B) << ", " << C << ", 0, 0, 0);\n";
         }
       o << "    }\n    __builtin_amdgcn_sched_barrier(0);\n";
@@ -350,7 +407,7 @@ GenKernel gen_gemm_phased(const KInfo& ki, GemmSpec& sp, int index) {
   s << "  __shared__ __attribute__((aligned(1024))) char smem[" << phased_smem(sp) << "];\n";
   if (sp.KG > 1) {
     s << "  const int kgrp = __builtin_amdgcn_readfirstlane(threadIdx.x / " << GT << ");  // which part of the k-tiles\n";
-    s << "  char* gsm_ = smem + kgrp * " << sp.PST * (sp.BM + sp.BN) * sp.BK * 2 << ";  // this group's operand stages\n";
+    s << "  char* gsm_ = smem + kgrp * " << sp.PST * (sp.BM + sp.BN) * sp.BK * dtype_bytes(sp.mtype) << ";  // this group's operand stages\n";
     s << "  const int tid = threadIdx.x % " << GT << ", l = tid & 63, wave = tid >> 6;\n";
   } else {
     s << "  char* gsm_ = smem;  // operand stages\n";

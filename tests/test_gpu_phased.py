@@ -17,6 +17,8 @@ torch = pytest.importorskip("torch")
 SHAPES = ["256,256,2,4,1,64,2", "256,128,2,4,1,64,3", "128,128,2,2,1,64,2", "128,128,2,4,1,64,4", "128,96,2,2,1,64,2",
           "128,96,4,2,1,64,5", "128,64,4,2,1,64,5", "128,64,2,2,1,64,3", "64,128,2,2,1,64,3", "64,64,2,2,1,64,4",
           "32,64,2,2,1,64,6", "32,64,2,2,2,64,6", "256,256,2,4,1,32,5", "128,96,2,2,2,32,5"]
+F32_SHAPES = ["64,128,2,2,1,32,2", "64,96,2,2,1,32,2", "64,64,2,2,1,32,2", "32,64,2,2,1,32,4", "32,32,2,2,1,32,4", "64,96,2,2,2,32,3",
+              "32,64,2,2,2,32,6", "32,32,2,2,2,32,6", "128,128,2,4,1,32,4"]
 SIZES = [(300, 264, 200), (1, 8, 8), (257, 520, 64), (128, 96, 1000), (33, 72, 456)]
 
 
@@ -67,13 +69,13 @@ def _check(r, x, k, dtype):
     if "R" in x:
         ref = ref + x["R"]
         mag = mag + x["R"].abs()
-    eps = 2.0 ** -11 if dtype == "f16" else 2.0 ** -8
+    eps = {"f16": 2.0 ** -11, "bf16": 2.0 ** -8, "f32": 2.0 ** -24}[dtype]
     bound = eps * ref.abs() * 1.01 + (k + 2) * 2.0 ** -24 * mag + 2.0 ** -24
     bad = (out - ref).abs() > bound
     assert not bool(bad.any()), f"{int(bad.sum())} of {bad.numel()} beyond the bound, worst {float(((out - ref).abs() / bound).max()):.2f}"
 
 
-@pytest.mark.parametrize("cfg", SHAPES)
+@pytest.mark.parametrize("cfg", SHAPES + F32_SHAPES)
 def test_phased_kernels_compile_without_spills(cfg, monkeypatch):
     """Each tile shape with a plain store and with a residual epilogue."""
     from paper_2406_09465_amd import codeobj
@@ -81,7 +83,7 @@ def test_phased_kernels_compile_without_spills(cfg, monkeypatch):
     monkeypatch.setenv("KORCH_GEMM_PHASED", cfg)
     bm, bn, wm, wn, kg, bk, st = map(int, cfg.split(","))
     for epi in ("", "residual"):
-        w, kernels = _graph(700, 520, 1032, "bf16", epi)
+        w, kernels = _graph(700, 520, 1032, "f32" if cfg in F32_SHAPES else "bf16", epi)
         p = Plan(w.graph, kernels)
         p.compile()
         (grid, block, lds) = p.kernel_launch(0)
@@ -92,8 +94,8 @@ def test_phased_kernels_compile_without_spills(cfg, monkeypatch):
 
 
 def test_phased_selection():
-    """Plain 16-bit products take the path; fp32 ones, operands computed in the
-    kernel, rows that are not 16-byte chunks and small short products do not."""
+    """Plain products take the path; rows that are not 16-byte chunks and small
+    short 16-bit products do not."""
     from paper_2406_09465_amd._abi import Plan
 
     def phased(m, n, k, dtype):
@@ -102,7 +104,8 @@ def test_phased_selection():
         return "offen lds" in p.kernel_source(0)
 
     assert phased(4096, 1024, 1024, "bf16") and phased(1576, 384, 1536, "f16") and phased(301, 264, 1000, "f16")
-    assert not phased(4096, 1024, 1024, "f32") and not phased(4096, 1024, 1020, "f16") and not phased(512, 512, 128, "f16")
+    assert phased(2048, 768, 3072, "f32") and phased(49, 100, 36, "f32") and not phased(512, 512, 510, "f32")
+    assert not phased(4096, 1024, 1020, "f16") and not phased(512, 512, 128, "f16")
 
 
 @pytest.mark.gpu
@@ -123,6 +126,27 @@ def test_phased_product(cfg, size, monkeypatch):
             r.launch_bound()
         torch.cuda.synchronize()
         assert torch.equal(first.view(torch.int16), r.outs[0].view(torch.int16))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("size", [(300, 264, 200), (1, 4, 4), (129, 100, 36), (70, 96, 1000), (33, 68, 452)],
+                         ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("cfg", F32_SHAPES)
+def test_phased_f32_product(cfg, size, monkeypatch):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    monkeypatch.setenv("KORCH_GEMM_PHASED", cfg)
+    m, n, k = size
+    for epi, batch in (("", 0), ("residual", 3)):
+        print(f"\n[case] phased f32 {cfg} {size} {epi} batch {batch}", flush=True)
+        r, x = _run(m, n, k, "f32", epi, batch, seed=m + n + k)
+        assert "offen lds" in r.plan.kernel_source(0)
+        _check(r, x, k, "f32")
+        first = r.outs[0].clone()
+        for _ in range(5):
+            r.launch_bound()
+        torch.cuda.synchronize()
+        assert torch.equal(first, r.outs[0])
 
 
 @pytest.mark.gpu
