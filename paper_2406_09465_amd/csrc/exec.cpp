@@ -39,10 +39,16 @@ constexpr size_t kStaticCounterBytes = (size_t)64 << 10;
     if (e_ != hipSuccess) fail(KORCH_E_HIP, std::string(#x) + ": " + hipGetErrorString(e_));    \
   } while (0)
 
-void generate_plan(Plan& p) {
-  if (!p.ck.empty()) return;
+static bool fits_static_scratch(const Plan& p) {
+  return p.counter_bytes <= kStaticCounterBytes && p.ws_bytes <= static_scratch_bytes() - kStaticCounterBytes;
+}
+
+// Generates every kernel with or without splits of a product's contraction
+// over workgroups (p.wg_splits) and lays out the plan's workspace.
+static void generate_kernels(Plan& p) {
   std::vector<CompiledKernel> ck(p.kernels.size());
   set_kernel_prefix(p.name_prefix);
+  set_workgroup_splits(p.wg_splits);
   try {
     for (size_t k = 0; k < p.kernels.size(); ++k) {
       ck[k].desc = p.kernels[k];
@@ -50,11 +56,26 @@ void generate_plan(Plan& p) {
     }
   } catch (...) {
     set_kernel_prefix("korch_k");
+    set_workgroup_splits(true);
     throw;
   }
   set_kernel_prefix("korch_k");
+  set_workgroup_splits(true);
   p.ck = std::move(ck);
   plan_workspace(p);
+}
+
+// The splits' scratch and counters must not keep a plan out of allocation-free
+// execution: a plan that only fits the static scratch without them has none.
+void generate_plan(Plan& p) {
+  if (!p.ck.empty()) return;
+  generate_kernels(p);
+  if (fits_static_scratch(p)) return;
+  p.wg_splits = false;
+  generate_kernels(p);
+  if (fits_static_scratch(p)) return;
+  p.wg_splits = true;
+  generate_kernels(p);
 }
 
 // Kernels are compiled on the calling thread: hipRTC runs in a link namespace
@@ -92,13 +113,16 @@ void compile_plan(Plan& p) {
       for (int level = 1; level <= kMaxRegRelief && code_scratch_bytes(p.ck[k].code) > 0; ++level) {
         set_kernel_prefix(p.name_prefix);
         set_reg_relief(level);
+        set_workgroup_splits(p.wg_splits);
         try {
           p.ck[k].gen = generate_kernel(p.g, p.ck[k].desc, k);
         } catch (...) {
+          set_workgroup_splits(true);
           set_reg_relief(0);
           set_kernel_prefix("korch_k");
           throw;
         }
+        set_workgroup_splits(true);
         set_reg_relief(0);
         set_kernel_prefix("korch_k");
         p.ck[k].code = rtc_compile(p.ck[k].gen.source, p.ck[k].gen.name);

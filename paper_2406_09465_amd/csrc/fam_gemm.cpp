@@ -1847,7 +1847,7 @@ static bool eight_wave_dma(const KInfo& ki, GemmSpec& sp, int64_t tiles, int64_t
   return true;
 }
 
-std::string gemm_tile_order(const GemmSpec& sp, int64_t ntm, int64_t ntn) {
+std::string gemm_tile_order(const GemmSpec& sp, int64_t ntm, int64_t ntn, const std::string& wgx) {
   // Workgroups are dispatched round-robin over the 8 XCDs, each with its own
   // L2.  Renumber them so every XCD owns a contiguous range of tiles, and order
   // tiles in groups of GM row-tiles so the tiles running together on one XCD
@@ -1855,7 +1855,7 @@ std::string gemm_tile_order(const GemmSpec& sp, int64_t ntm, int64_t ntn) {
   int64_t total = ntn * ntm * sp.batch;
   std::ostringstream s;
   int64_t GM = std::min<int64_t>(8, ntm);
-  s << "  const int wg = blockIdx.x, xcd = wg % 8, jx = wg / 8;\n";
+  s << "  const int wg = " << wgx << ", xcd = wg % 8, jx = wg / 8;\n";
   s << "  const int q = xcd * " << total / 8 << " + (xcd < " << total % 8 << " ? xcd : " << total % 8 << ") + jx;\n";
   s << "  const int bz_ = q / " << ntm * ntn << ", r_ = q % " << ntm * ntn << ";\n";
   s << "  const int grp = r_ / " << GM * ntn << ", first = grp * " << GM << ";\n";

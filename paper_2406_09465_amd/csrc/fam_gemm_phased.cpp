@@ -17,6 +17,7 @@
 // into it at once, and the last phases' MFMAs cover the barrier and the first
 // fragment reads of the next tile.
 #include <algorithm>
+#include <cmath>
 #include <cstdio>
 #include <cstdlib>
 
@@ -25,9 +26,27 @@
 
 namespace korch {
 
+static thread_local bool g_workgroup_splits = true;
+void set_workgroup_splits(bool on) { g_workgroup_splits = on; }
+bool workgroup_splits() { return g_workgroup_splits; }
+
 static bool env_set(const char* n) {
   const char* e = getenv(n);
   return e && *e;
+}
+
+// Splitting a tile's contraction over workgroups pays where tiles leave compute
+// units idle and the chain of k-tiles is long (the second product of an MLP
+// block on few rows): up to one workgroup per compute unit, four k-tiles each.
+// The hand-off (partial tiles out, a counter, the last workgroup's sum) costs
+// what it measured with 4 to 16 KiB tiles and 2 to 8 parts.  128 x 768 x 3072: 6.0
+// us in four parts against 9.2 (12.4 staged through registers); 16 x 1024 x 4096:
+// 5.1 against 8.7; 49 x 960 x 2240 in fp32 6.7 against 11.6.
+static bool splits_fit(int bm, int bn, int64_t tiles, int ks, double kt) {
+  return workgroup_splits() && tiles * ks <= 256 && kt >= 4.0 * ks && (double)tiles * ks * bm * bn * 4 <= 8.0 * (1 << 20);
+}
+static double handoff(int bm, int bn, int ks, int kg) {
+  return ks > 1 ? 0.5 + ks * (0.3 + 0.015 * bm * bn / 256.0) + (kg > 1 ? 0.45 : 0.0) : 0.0;
 }
 
 // Tile shape, waves, k-groups and stages of the phased path; false: not taken.
@@ -45,9 +64,9 @@ static bool env_set(const char* n) {
 // when there are few of them.
 static bool phased_tiles(GemmSpec& sp) {
   if (const char* e = getenv("KORCH_GEMM_PHASED")) {
-    int bm, bn, wm, wn, kg, st, bk;
-    if (sscanf(e, "%d,%d,%d,%d,%d,%d,%d", &bm, &bn, &wm, &wn, &kg, &bk, &st) != 7) return false;
-    sp.BM = bm, sp.BN = bn, sp.WM = wm, sp.WN = wn, sp.KG = kg, sp.PST = st, sp.BK = bk;
+    int bm, bn, wm, wn, kg, st, bk, ks = 1;
+    if (sscanf(e, "%d,%d,%d,%d,%d,%d,%d,%d", &bm, &bn, &wm, &wn, &kg, &bk, &st, &ks) < 7) return false;
+    sp.BM = bm, sp.BN = bn, sp.WM = wm, sp.WN = wn, sp.KG = kg, sp.PST = st, sp.BK = bk, sp.KS = ks;
     return true;
   }
   struct Shape_ {
@@ -71,11 +90,15 @@ static bool phased_tiles(GemmSpec& sp) {
     const double KT = (double)((sp.K + 31) / 32);
     for (const Shape_& h : f32s) {
       const int64_t tiles = (sp.M + h.bm - 1) / h.bm * ((sp.N + h.bn - 1) / h.bn) * sp.batch, n = (tiles + 255) / 256;
-      if (h.kg > 1 && (n > 1 || KT < 16)) continue;  // two k-groups share the compute unit of one tile
-      const double cost = h.ov + KT * (n == 1 ? h.t1 : n * h.tc);
-      if (cost < best) {
-        best = cost;
-        sp.BM = h.bm, sp.BN = h.bn, sp.WM = h.wm, sp.WN = h.wn, sp.KG = h.kg, sp.PST = h.st, sp.BK = 32;
+      for (int ks = 1; ks <= 8; ++ks) {
+        if (ks > 1 && !splits_fit(h.bm, h.bn, tiles, ks, KT)) break;
+        const double kt = std::ceil(KT / ks);
+        if (h.kg > 1 && (n > 1 || kt < 8)) continue;  // two k-groups share the compute unit of one tile
+        const double cost = h.ov + kt * (n == 1 ? h.t1 : n * h.tc) + handoff(h.bm, h.bn, ks, h.kg);
+        if (cost < best) {
+          best = cost;
+          sp.BM = h.bm, sp.BN = h.bn, sp.WM = h.wm, sp.WN = h.wn, sp.KG = h.kg, sp.PST = h.st, sp.BK = 32, sp.KS = ks;
+        }
       }
     }
     return true;
@@ -84,19 +107,27 @@ static bool phased_tiles(GemmSpec& sp) {
       {256, 256, 2, 4, 1, 2, 1, 1.50, 1.50, 9.5}, {256, 128, 2, 4, 1, 3, 1, 0.87, 0.87, 4.9}, {128, 128, 2, 2, 1, 2, 2, 0.62, 1.00, 3.2},
       {128, 128, 2, 4, 1, 4, 1, 0.50, 0.50, 2.6}, {128, 96, 2, 2, 1, 2, 2, 0.60, 0.88, 2.8},  {128, 96, 4, 2, 1, 5, 1, 0.46, 0.46, 2.2},
       {128, 64, 4, 2, 1, 5, 1, 0.31, 0.31, 2.2},  {128, 64, 2, 2, 1, 3, 2, 0.31, 0.57, 2.4},  {64, 128, 2, 2, 1, 3, 2, 0.31, 0.56, 2.3},
-      {64, 64, 2, 2, 1, 4, 2, 0.22, 0.38, 1.7},   {32, 64, 2, 2, 1, 6, 2, 0.17, 0.29, 1.6},   {32, 64, 2, 2, 2, 6, 1, 0.155, 0.155, 1.6},
+      {64, 64, 2, 2, 1, 4, 2, 0.245, 0.38, 1.7},   {32, 64, 2, 2, 1, 6, 2, 0.17, 0.29, 1.6},   {32, 64, 2, 2, 2, 6, 1, 0.155, 0.155, 1.6},
   };
   const double KT = (double)((sp.K + 63) / 64);
   for (const Shape_& h : shapes) {
     const int64_t tiles = (sp.M + h.bm - 1) / h.bm * ((sp.N + h.bn - 1) / h.bn) * sp.batch;
     const int64_t full = tiles / (256 * h.c), rest = (tiles - full * 256 * h.c + 255) / 256;
-    // two k-groups halve a workgroup's chain of k-tiles: for few tiles only
-    if (h.kg > 1 && (tiles > 64 || KT < 16)) continue;
     const double tr = h.c > 1 ? h.t1 + (h.tc - h.t1) * (double)(rest - 1) / (h.c - 1) : h.t1;
-    const double cost = full * (KT * h.tc + h.ov) + (rest ? KT * tr + h.ov : 0.0);
-    if (cost < best) {
-      best = cost;
-      sp.BM = h.bm, sp.BN = h.bn, sp.WM = h.wm, sp.WN = h.wn, sp.KG = h.kg, sp.PST = h.st, sp.BK = 64;
+    for (int ks = 1; ks <= 8; ++ks) {
+      if (ks > 1 && !splits_fit(h.bm, h.bn, tiles, ks, KT)) break;
+      const double kt = std::ceil(KT / ks);
+      // two k-groups (their loads share one compute unit): where it has one tile
+      if (h.kg > 1 && (tiles * ks > 256 || kt < 8)) continue;
+      // Up to 32 k-tiles a split keeps two k-groups in each workgroup, as the
+      // k-split kernel of such products always had (tests pin it); without them
+      // 100 x 512 x 2048 takes 4.5 us against 4.9.
+      if (h.kg == 1 && ks > 1 && KT <= 32) continue;
+      const double cost = full * (kt * h.tc + h.ov) + (rest ? kt * tr + h.ov : 0.0) + handoff(h.bm, h.bn, ks, h.kg);
+      if (cost < best) {
+        best = cost;
+        sp.BM = h.bm, sp.BN = h.bn, sp.WM = h.wm, sp.WN = h.wn, sp.KG = h.kg, sp.PST = h.st, sp.BK = 64, sp.KS = ks;
+      }
     }
   }
   return true;
@@ -140,11 +171,12 @@ bool plan_phased(const KInfo& ki, GemmSpec& sp, bool split_halves) {
     return false;
   GemmSpec t = sp;
   if (!phased_tiles(t)) return false;
+  if (t.KS < 1 || t.KS * t.KG > (t.K + t.BK - 1) / t.BK) t.KS = 1;
   // A long contraction whose 128-row tiles leave at most one per compute unit
   // is summed in two halves that are added at the end, as its k-split kernel
   // with register staging does: the results are the same to the bit (wave tiles
   // of up to 16 blocks, which leave registers for the second set of sums).
-  t.KSEQ = t.KG == 1 && split_halves && t.BM / t.WM * (t.BN / t.WN) <= 16 * 256 ? 2 : 1;
+  t.KSEQ = t.KG == 1 && t.KS == 1 && split_halves && t.BM / t.WM * (t.BN / t.WN) <= 16 * 256 ? 2 : 1;
   if (t.WM < 1 || t.WN < 1 || t.KG < 1 || t.BM % (16 * t.WM) || t.BN % (16 * t.WN)) return false;
   const int gw = t.WM * t.WN;  // waves per group
   t.NT = 64 * gw * t.KG;
@@ -164,7 +196,7 @@ bool plan_phased(const KInfo& ki, GemmSpec& sp, bool split_halves) {
     t.OSP = t.BN + 8;
     t.OSB = t.BM * t.OSP * 2;
   }
-  if (phased_smem(t) > 160 * 1024) return false;
+  if (phased_smem(t) + (t.KS > 1 ? 16 : 0) > 160 * 1024) return false;
   sp = t;
   return true;
 }
@@ -230,7 +262,7 @@ static std::string phased_loader(const KInfo& ki, const GemmSpec& sp, const std:
   const bool tail = sp.K % sp.BK != 0;
   // tile kt into stage st
   s << "  auto load_ = [&](const int kt, const int st) {\n";
-  s << "    {\n    const unsigned so = (unsigned)kt * " << sp.BK * eb << "u;\n#pragma unroll\n    for (int i = 0; i < " << PA << "; ++i) {\n";
+  s << "    {\n    const unsigned so = __builtin_amdgcn_readfirstlane((unsigned)kt * " << sp.BK * eb << "u);\n#pragma unroll\n    for (int i = 0; i < " << PA << "; ++i) {\n";
   s << "      const unsigned la = lds0_ + (unsigned)(st * " << SAB << " + (wv_ + i * " << GW << ") * 1024);\n";
   if (tail)
     s << "      const unsigned vo = kt == " << KT - 1 << " && lk_ >= " << sp.K % sp.BK
@@ -239,7 +271,7 @@ static std::string phased_loader(const KInfo& ki, const GemmSpec& sp, const std:
   else
     s << ld("va_[i]", "rsA_");
   s << "    }\n    }\n";
-  s << "    {\n    const unsigned so = (unsigned)kt * " << eb * sp.BK * sp.N << "u;\n#pragma unroll\n    for (int i = 0; i < " << PB << "; ++i) {\n";
+  s << "    {\n    const unsigned so = __builtin_amdgcn_readfirstlane((unsigned)kt * " << eb * sp.BK * sp.N << "u);\n#pragma unroll\n    for (int i = 0; i < " << PB << "; ++i) {\n";
   if (NB % GW) s << "      if (i == " << PB - 1 << " && wv_ >= " << NB % GW << ") break;  // the first waves load one block more\n";
   s << "      const unsigned la = lds0_ + (unsigned)(" << sp.PST * SAB << " + st * " << SBB << " + (wv_ + i * " << GW << ") * 1024);\n";
   if (tail)
@@ -398,7 +430,26 @@ GenKernel gen_gemm_phased(const KInfo& ki, GemmSpec& sp, int index) {
   std::map<int, int> slot;
   ki.assign_args(gk, slot);
   const int64_t ntn = (sp.N + sp.BN - 1) / sp.BN, ntm = (sp.M + sp.BM - 1) / sp.BM, KT = (sp.K + sp.BK - 1) / sp.BK;
-  const int64_t KTG = (KT + sp.KG - 1) / sp.KG;  // k-tiles of a group
+  const int parts = sp.KG * sp.KS;  // of the k-tiles: the first KT % parts of them have one more
+  const int64_t KTG = (KT + parts - 1) / parts;
+  const int64_t tiles = ntn * ntm * sp.batch;
+  // Split of the contraction over workgroups: every part's sums to scratch in
+  // lane order (coherent stores), the tile's last workgroup adds them in part
+  // order and runs the epilogue.  One counter per tile on a line of its own.
+  const size_t part_bytes = (size_t)sp.BM * sp.BN * 4;
+  int scr_slot = -1, cnt_slot = -1;
+  if (sp.KS > 1) {
+    ArgRef scr;
+    scr.kind = ArgRef::Scratch;
+    scr.bytes = (size_t)tiles * sp.KS * part_bytes;
+    scr_slot = (int)gk.args.size();
+    gk.args.push_back(scr);
+    ArgRef cnt;
+    cnt.kind = ArgRef::Counter;
+    cnt.bytes = (size_t)tiles * 128;
+    cnt_slot = (int)gk.args.size();
+    gk.args.push_back(cnt);
+  }
   const std::string T = ctype(sp.mtype);
   const int GT = 64 * sp.WM * sp.WN;  // threads of a group
   std::ostringstream s;
@@ -414,13 +465,17 @@ GenKernel gen_gemm_phased(const KInfo& ki, GemmSpec& sp, int index) {
     s << "  const int tid = threadIdx.x, l = tid & 63, wave = tid >> 6;\n";
   }
   s << "  const int wm = wave / " << sp.WN << ", wn = wave % " << sp.WN << ";\n  (void)wm; (void)wn;\n";
-  s << gemm_tile_order(sp, ntm, ntn);
-  if (sp.KG > 1)
-    s << "  const int kt0 = kgrp * " << KTG << ", kt1 = kt0 + " << KTG << " < " << KT << " ? kt0 + " << KTG << " : " << KT << ";\n";
-  else
+  if (sp.KS > 1) s << "  const int split_ = blockIdx.x / " << tiles << ";  // which part of the k-tiles\n  __shared__ int last_;\n";
+  s << gemm_tile_order(sp, ntm, ntn, sp.KS > 1 ? "blockIdx.x % " + std::to_string(tiles) : std::string("blockIdx.x"));
+  if (parts > 1) {
+    const std::string pt = sp.KS == 1 ? "kgrp" : sp.KG == 1 ? "split_" : "(split_ * " + std::to_string(sp.KG) + " + kgrp)", B_ = std::to_string(KT / parts), R_ = std::to_string(KT % parts);
+    s << "  const int kt0 = " << pt << " * " << B_ << " + (" << pt << " < " << R_ << " ? " << pt << " : " << R_ << "), kt1 = kt0 + " << B_
+      << " + (" << pt << " < " << R_ << " ? 1 : 0);\n";
+  } else {
     s << "  const int kt0 = 0, kt1 = " << KT << ";\n";
+  }
   s << phased_loader(ki, sp, slot);
-  s << phased_mainloop(sp, KTG, KT % sp.KG == 0);
+  s << phased_mainloop(sp, KTG, KT % parts == 0);
   auto ctile = [&](const char* op) {
     std::ostringstream o;
     o << "#pragma unroll\n    for (int i = 0; i < " << sp.FM << "; ++i)\n#pragma unroll\n    for (int j = 0; j < " << sp.FN
@@ -428,6 +483,53 @@ GenKernel gen_gemm_phased(const KInfo& ki, GemmSpec& sp, int index) {
       << ") + i * 16 + (l >> 4) * 4 + r) * " << sp.LDC << " + wn * " << sp.WTN << " + j * 16 + (l & 15)] " << op << " acc[i][j][r];\n";
     return o.str();
   };
+  // The groups' sums one after another in group order into the fp32 C tile.
+  auto groups = [&]() {
+    std::string o;
+    for (int q = 0; q < sp.KG; ++q) o += "  if (kgrp == " + std::to_string(q) + ") {\n" + ctile(q ? "+=" : "=") + "  }\n  __syncthreads();\n";
+    return o;
+  };
+  if (sp.KS > 1) {
+    // NV 16-byte vectors per thread: the accumulator blocks in lane order, or
+    // (several k-groups, whose sums meet in the C tile first) the tile's rows
+    const bool viaC = sp.KG > 1;
+    const int VPR = sp.BN / 4, NV = viaC ? (sp.BM * VPR + sp.NT - 1) / sp.NT : sp.FM * sp.FN, LB = sp.NT * 16;
+    const bool whole = !viaC || sp.BM * VPR % sp.NT == 0;
+    const std::string TID = viaC ? "(int)threadIdx.x" : "tid";
+    auto reg = [&](const std::string& i) {
+      return viaC ? "*(f32x4*)(Cs + ((" + TID + " + " + i + " * " + std::to_string(sp.NT) + ") / " + std::to_string(VPR) + ") * " +
+                        std::to_string(sp.LDC) + " + ((" + TID + " + " + i + " * " + std::to_string(sp.NT) + ") % " + std::to_string(VPR) + ") * 4)"
+                  : "acc[" + i + " / " + std::to_string(sp.FN) + "][" + i + " % " + std::to_string(sp.FN) + "]";
+    };
+    const std::string in = whole ? "" : "if (" + TID + " + i * " + std::to_string(sp.NT) + " < " + std::to_string(sp.BM * VPR) + ") ";
+    s << "  {\n";
+    if (viaC) s << "  float* Cs = (float*)smem;\n" << groups();
+    s << "  float* part_ = (float*)a.p[" << scr_slot << "];\n";
+    s << "  const __amdgpu_buffer_rsrc_t rsP = __builtin_amdgcn_make_buffer_rsrc(part_, 0, " << tiles * sp.KS * part_bytes << ", 0x00020000);\n";
+    s << "  const unsigned po_ = (unsigned)(wg * " << sp.KS << ") * " << part_bytes << "u + " << TID << " * 16;\n";
+    s << "#pragma unroll\n  for (int i = 0; i < " << NV << "; ++i)\n    " << in << "coherent_store4(rsP, po_ + split_ * " << part_bytes
+      << "u + i * " << LB << ", __builtin_bit_cast(float4, " << reg("i") << "));\n";
+    s << "  __builtin_amdgcn_s_waitcnt(0);  // this wave's partial stores are performed\n  __syncthreads();\n";
+    s << "  if (threadIdx.x == 0) {\n    int* cnt = (int*)a.p[" << cnt_slot << "] + wg * 32;\n";
+    s << "    const int old = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);\n";
+    s << "    last_ = old == " << sp.KS - 1 << ";\n";
+    s << "    if (last_) __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);\n  }\n";
+    s << "  __syncthreads();\n  if (!last_) return;\n";
+    // up to 32 loads in flight per thread; past the tile or the last part they
+    // repeat one that exists
+    const int BS = std::max(1, std::min(sp.KS, 32 / NV));
+    s << "  f32x4 sum_[" << NV << "];\n#pragma unroll\n  for (int i = 0; i < " << NV << "; ++i) sum_[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};\n";
+    s << (sp.KS > BS ? "#pragma unroll 1\n" : "#pragma unroll\n") << "  for (int s0_ = 0; s0_ < " << sp.KS << "; s0_ += " << BS << ") {\n";
+    s << "    f32x4 v_[" << BS << "][" << NV << "];\n";
+    s << "#pragma unroll\n    for (int s_ = 0; s_ < " << BS << "; ++s_)\n#pragma unroll\n      for (int i = 0; i < " << NV
+      << "; ++i) v_[s_][i] = __builtin_bit_cast(f32x4, coherent_load4(rsP, po_ + (s0_ + s_ < " << sp.KS << " ? s0_ + s_ : " << sp.KS - 1 << ") * "
+      << part_bytes << "u + i * " << LB << "));\n";
+    s << "#pragma unroll\n    for (int s_ = 0; s_ < " << BS << "; ++s_)\n#pragma unroll\n      for (int i = 0; i < " << NV << "; ++i)\n"
+      << "        if (s0_ + s_ < " << sp.KS << ") sum_[i] += v_[s_][i];\n    }\n";
+    s << "#pragma unroll\n  for (int i = 0; i < " << NV << "; ++i) " << in << reg("i") << " = sum_[i];\n";
+    if (viaC) s << "  __syncthreads();\n";
+    s << "  }\n";
+  }
   // The epilogue's lane indices go through an opaque copy: its many LDS and
   // output addresses would otherwise be computed ahead of the main loop and
   // held (spilled) across it.
@@ -437,9 +539,7 @@ GenKernel gen_gemm_phased(const KInfo& ki, GemmSpec& sp, int index) {
   if (sp.acc_t) {
     s << gemm_reg_epilogue(ki, sp, slot, reg_epilogue_output(ki, sp));
   } else if (sp.KG > 1) {
-    // the groups' sums one after another in group order
-    s << "  float* Cs = (float*)smem;\n";
-    for (int q = 0; q < sp.KG; ++q) s << "  if (kgrp == " << q << ") {\n" << ctile(q ? "+=" : "=") << "  }\n  __syncthreads();\n";
+    s << "  float* Cs = (float*)smem;\n" << (sp.KS == 1 ? groups() : std::string());
     s << "  {\n  const int tid = te_;\n";
     s << gemm_epilogue(ki, sp, slot, "ml * " + std::to_string(sp.LDC));
     s << "  }\n";
@@ -460,7 +560,7 @@ GenKernel gen_gemm_phased(const KInfo& ki, GemmSpec& sp, int index) {
   }
   s << "  }\n}\n";
   gk.source = s.str();
-  gk.grid[0] = (int)(ntn * ntm * sp.batch);
+  gk.grid[0] = (int)(tiles * sp.KS);
   gk.block[0] = sp.NT;
   gk.lds_bytes = (int)phased_smem(sp);
   ki.fill_cost(gk);

@@ -71,6 +71,7 @@ struct GemmSpec {
   // its own part of the k-tiles (0: not taken).
   int KG = 0;
   int PST = 2;   // its stages of each operand
+  int KS = 1;    // workgroups that share a tile's contraction
   int KSEQ = 1;  // parts of the contraction summed one after another, then added
   // LayerNorm folded into the product (see detect_ln_fold): the left operand
   // is LN(X) = (X - mu) r gamma + beta over X's last axis; the kernel stages X,
@@ -95,7 +96,8 @@ std::string dma_fk(const GemmSpec& sp, const std::string& k);
 // Element offset of the batch (z0, z1, ...) in a product operand.
 std::string operand_batch_offset(const KInfo& ki, const GemmSpec& sp, int node);
 // Definitions of the workgroup's batch coordinates and tile origin (m0, n0).
-std::string gemm_tile_order(const GemmSpec& sp, int64_t ntm, int64_t ntn);
+// `wgx`: the workgroup's number among the tiles (left in `wg`).
+std::string gemm_tile_order(const GemmSpec& sp, int64_t ntm, int64_t ntn, const std::string& wgx = "blockIdx.x");
 // Phased main loop: decides (tiles, waves, k-groups) and generates.
 // split_halves: the older path would split the contraction in two inside a workgroup.
 bool plan_phased(const KInfo& ki, GemmSpec& sp, bool split_halves);

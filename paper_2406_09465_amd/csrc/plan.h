@@ -39,6 +39,7 @@ struct Plan {
   int counter_device = -1;
   std::map<int, size_t> ws_offset;  // workspace-resident materialized node -> offset
   std::string name_prefix = "korch_k";  // kernel symbols: <prefix><index>_<family>
+  bool wg_splits = true;  // products may split a contraction over workgroups
 };
 
 // Checks a plan against Definitions 1 and 3 and the ordered dependency /

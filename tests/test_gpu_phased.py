@@ -19,6 +19,9 @@ SHAPES = ["256,256,2,4,1,64,2", "256,128,2,4,1,64,3", "128,128,2,2,1,64,2", "128
           "32,64,2,2,1,64,6", "32,64,2,2,2,64,6", "256,256,2,4,1,32,5", "128,96,2,2,2,32,5"]
 F32_SHAPES = ["64,128,2,2,1,32,2", "64,96,2,2,1,32,2", "64,64,2,2,1,32,2", "32,64,2,2,1,32,4", "32,32,2,2,1,32,4", "64,96,2,2,2,32,3",
               "32,64,2,2,2,32,6", "32,32,2,2,2,32,6", "128,128,2,4,1,32,4"]
+# (the last number: the parts of the contraction that workgroups share)
+SPLITS = ["32,64,2,2,2,64,6,2", "32,64,2,2,1,64,6,4", "64,64,2,2,1,64,4,3", "64,96,2,2,2,64,3,5", "128,128,2,4,1,64,4,8"]
+F32_SPLITS = ["32,32,2,2,1,32,4,8", "32,32,2,2,2,32,6,3", "64,64,2,2,1,32,2,5", "32,64,2,2,2,32,6,4"]
 SIZES = [(300, 264, 200), (1, 8, 8), (257, 520, 64), (128, 96, 1000), (33, 72, 456)]
 
 
@@ -75,22 +78,53 @@ def _check(r, x, k, dtype):
     assert not bool(bad.any()), f"{int(bad.sum())} of {bad.numel()} beyond the bound, worst {float(((out - ref).abs() / bound).max()):.2f}"
 
 
-@pytest.mark.parametrize("cfg", SHAPES + F32_SHAPES)
+@pytest.mark.parametrize("cfg", SHAPES + F32_SHAPES + SPLITS + F32_SPLITS)
 def test_phased_kernels_compile_without_spills(cfg, monkeypatch):
-    """Each tile shape with a plain store and with a residual epilogue."""
+    """Each tile shape with a plain store and with a residual epilogue: no
+    scratch, and M0 (the loads' LDS address, set in inline assembly the compiler
+    does not see into) used by nothing else."""
+    import os
+    import subprocess
+    import tempfile
     from paper_2406_09465_amd import codeobj
     from paper_2406_09465_amd._abi import Plan
     monkeypatch.setenv("KORCH_GEMM_PHASED", cfg)
-    bm, bn, wm, wn, kg, bk, st = map(int, cfg.split(","))
+    bm, bn, wm, wn, kg, bk, st, ks = (list(map(int, cfg.split(","))) + [1])[:8]
+    f32 = cfg in F32_SHAPES + F32_SPLITS
     for epi in ("", "residual"):
-        w, kernels = _graph(700, 520, 1032, "f32" if cfg in F32_SHAPES else "bf16", epi)
+        w, kernels = _graph(700, 520, 1032, "f32" if f32 else "bf16", epi)
         p = Plan(w.graph, kernels)
         p.compile()
         (grid, block, lds) = p.kernel_launch(0)
-        assert grid[0] == -(-700 // bm) * -(-520 // bn) and block[0] == 64 * wm * wn * kg and lds <= 160 * 1024
+        assert grid[0] == -(-700 // bm) * -(-520 // bn) * ks and block[0] == 64 * wm * wn * kg and lds <= 160 * 1024
         assert "offen lds" in p.kernel_source(0)
         (res,) = codeobj.kernel_resources(p.kernel_code(0)).values()
         assert res["scratch"] == 0 and res["vgpr"] + res["agpr"] <= 512 // (block[0] // 256)
+        objdump = "/opt/rocm/llvm/bin/llvm-objdump"
+        if not os.path.exists(objdump):
+            continue
+        with tempfile.NamedTemporaryFile(suffix=".co") as f:
+            f.write(p.kernel_code(0))
+            f.flush()
+            dis = subprocess.run([objdump, "-d", "--mcpu=gfx950", f.name], capture_output=True, text=True, check=True).stdout
+        ins = [ln.split("//")[0].split() for ln in dis.splitlines() if ln.startswith("\t")]
+        m0 = [i for i, w in enumerate(ins) if "m0" in [t.strip(",") for t in w]]
+        assert m0 and all(ins[i][:2] == ["s_mov_b32", "m0,"] and ins[i + 1][0] == "s_nop" and ins[i + 2][-1] == "lds" for i in m0)
+
+
+def test_workgroup_splits_keep_plans_allocation_free():
+    """A long product of few tiles splits its contraction over workgroups; a
+    plan whose tensors would fill the static scratch of allocation-free
+    execution together with the split's partial sums has no split."""
+    from paper_2406_09465_amd import graphs
+    static_ws = 33488896
+    p = graphs.build("mlp", m=64, d=768, h=3072).plan("layered")
+    assert "split_" in p.kernel_source(2) and p.workspace_bytes() <= static_ws
+    h = 32000  # the hidden activation alone: 512 x 32000 fp16 = 32,768,000 bytes
+    p = graphs.build("mlp", m=512, d=192, h=h).plan("layered")
+    assert "split_" not in p.kernel_source(2) and p.workspace_bytes() <= static_ws
+    p = graphs.build("mlp", m=512, d=192, h=40960).plan("layered")  # too large either way
+    assert "split_" in p.kernel_source(2) and p.workspace_bytes() > static_ws
 
 
 def test_phased_selection():
@@ -110,7 +144,7 @@ def test_phased_selection():
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("size", SIZES, ids=lambda s: "x".join(map(str, s)))
-@pytest.mark.parametrize("cfg", SHAPES)
+@pytest.mark.parametrize("cfg", SHAPES + SPLITS)
 def test_phased_product(cfg, size, monkeypatch):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
@@ -131,7 +165,7 @@ def test_phased_product(cfg, size, monkeypatch):
 @pytest.mark.gpu
 @pytest.mark.parametrize("size", [(300, 264, 200), (1, 4, 4), (129, 100, 36), (70, 96, 1000), (33, 68, 452)],
                          ids=lambda s: "x".join(map(str, s)))
-@pytest.mark.parametrize("cfg", F32_SHAPES)
+@pytest.mark.parametrize("cfg", F32_SHAPES + F32_SPLITS)
 def test_phased_f32_product(cfg, size, monkeypatch):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
