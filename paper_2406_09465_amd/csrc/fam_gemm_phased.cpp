@@ -110,6 +110,17 @@ static bool phased_tiles(GemmSpec& sp) {
       {64, 64, 2, 2, 1, 4, 2, 0.245, 0.38, 1.7},   {32, 64, 2, 2, 1, 6, 2, 0.17, 0.29, 1.6},   {32, 64, 2, 2, 2, 6, 1, 0.155, 0.155, 1.6},
   };
   const double KT = (double)((sp.K + 63) / 64);
+  if (KT <= 2 && sp.N % 8) {
+    // One or two k-tiles and output rows that take narrow stores: the stores are
+    // the time, issued best by many small workgroups (1477 x 1477 x 128: 128 x 96
+    // tiles 6.1 us, 64 x 128 7.1, 64 x 64 5.5; 2001 x 501 x 96: 64 x 64 4.4, 32 x 64 3.7).
+    // One k-step of 32 has nothing to stage ahead (1477 x 1477 x 16: 4.2 us with
+    // register staging, 4.7 here).
+    if (sp.K <= 32) return false;
+    sp.BM = (sp.M + 63) / 64 * ((sp.N + 63) / 64) * sp.batch <= 256 ? 32 : 64;
+    sp.BN = 64, sp.WM = sp.WN = 2, sp.KG = 1, sp.PST = 2, sp.BK = 64, sp.KS = 1;
+    return true;
+  }
   for (const Shape_& h : shapes) {
     const int64_t tiles = (sp.M + h.bm - 1) / h.bm * ((sp.N + h.bn - 1) / h.bn) * sp.batch;
     const int64_t full = tiles / (256 * h.c), rest = (tiles - full * 256 * h.c + 255) / 256;
@@ -147,6 +158,20 @@ static size_t phased_smem(const GemmSpec& sp) {
   return std::max(st, sp.KG > 1 ? (size_t)sp.BM * sp.LDC * 4 : (size_t)2 * sp.WM * 16 * phased_band(sp) * sp.LDC * 4);
 }
 
+// The stored tensor whose last two dimensions the kernel transposes to form the
+// right operand (attention's keys), or -1.
+static int transposed_source(const KInfo& ki, const GemmSpec& sp) {
+  const Node& n = ki.g.nodes[sp.Bs[0]];
+  const int r = (int)n.shape.size();
+  if (n.op != KORCH_TRANSPOSE || r < 2 || ki.in.count(n.in[0]) || sp.pro.size() != 1) return -1;
+  for (int d = 0; d + 2 < r; ++d)
+    if (n.attrs.perm[d] != d) return -1;
+  if (n.attrs.perm[r - 2] != r - 1 || n.attrs.perm[r - 1] != r - 2) return -1;
+  for (int o : ki.k.outs)
+    if (o == sp.Bs[0]) return -1;
+  return n.in[0];
+}
+
 bool plan_phased(const KInfo& ki, GemmSpec& sp, bool split_halves) {
   sp.KG = 0;
   // the switches of the older staging paths ask for those paths
@@ -154,10 +179,13 @@ bool plan_phased(const KInfo& ki, GemmSpec& sp, bool split_halves) {
                         "KORCH_GEMM_DMA_KSPLIT", "KORCH_GEMM_DMA_2STAGE", "KORCH_GEMM_DMA_A3", "KORCH_GEMM_DMA_STAGES",
                         "KORCH_GEMM_SPLIT_STEPS"})
     if (env_set(n)) return false;
-  if (sp.conv || sp.lnf || sp.mms.size() != 1 || sp.Bs.size() != 1 || !sp.b_kn) return false;
+  if (sp.conv || sp.lnf || sp.mms.size() != 1 || sp.Bs.size() != 1 || !sp.side.empty() || !sp.rowred.empty()) return false;
   const int eb = dtype_bytes(sp.mtype), CE = 16 / eb;
-  if (ki.in.count(sp.A) || ki.in.count(sp.Bs[0])) return false;  // operands computed in the kernel
-  if (sp.K % CE || sp.N % CE) return false;                      // 16-byte chunks of rows
+  if (ki.in.count(sp.A)) return false;  // operands computed in the kernel
+  const int bt = ki.in.count(sp.Bs[0]) ? transposed_source(ki, sp) : -1;
+  if (ki.in.count(sp.Bs[0]) && bt < 0) return false;
+  // rows start on whole dwords (what a load to LDS needs; 16 bytes are read from any)
+  if (sp.K * eb % 4 || (bt < 0 && sp.N * eb % 4)) return false;
   // buffer loads: byte offsets below 2 GiB from a batch's operand
   if ((double)sp.M * sp.K * eb >= 2147483648.0 || (double)sp.K * sp.N * eb >= 2147483648.0) return false;
   // Products that 192-wide tiles divide into whole rounds keep those tiles and
@@ -170,6 +198,7 @@ bool plan_phased(const KInfo& ki, GemmSpec& sp, bool split_halves) {
       sp.N % sp.BN == 0)
     return false;
   GemmSpec t = sp;
+  t.bt = bt;
   if (!phased_tiles(t)) return false;
   if (t.KS < 1 || t.KS * t.KG > (t.K + t.BK - 1) / t.BK) t.KS = 1;
   // A long contraction whose 128-row tiles leave at most one per compute unit
@@ -187,7 +216,7 @@ bool plan_phased(const KInfo& ki, GemmSpec& sp, bool split_halves) {
   t.FM = t.WTM / 16, t.FN = t.WTN / 16;
   if (t.PST < 2 || t.PST > 12) return false;
   t.LDC = t.BN + 4;
-  if (CE == 8 && !dma_b_swizzle(t.BN / 8, t.dx0, t.dx1, t.dx3)) return false;
+  if (CE == 8 && bt < 0 && !dma_b_swizzle(t.BN / 8, t.dx0, t.dx1, t.dx3)) return false;
   t.acc_t = false;
   t.OSP = t.OSB = 0;
   t.CROWS = 0;
@@ -242,7 +271,7 @@ static std::string phased_loader(const KInfo& ki, const GemmSpec& sp, const std:
       << "_), __builtin_amdgcn_readfirstlane((int)((p" << X << "_ >> 32) & 0xffff)), " << (long long)bytes << ", 0x00020000};\n";
   };
   rsrc("A", sp.A, sp.M * sp.K * eb);
-  rsrc("B", sp.Bs[0], sp.K * sp.N * eb);
+  rsrc("B", sp.bt >= 0 ? sp.bt : sp.Bs[0], sp.K * sp.N * eb);
   // k of this lane's left chunk within a tile (its position holds chunk c ^ g(row))
   s << "  const int lk_ = " << (CR == 8 ? "((l & 7) ^ (l >> 3)) * " : "((l & 3) ^ ((l >> 3) & 2)) * ") << CE << ";\n";
   s << "  unsigned va_[" << PA << "], vb_[" << PB << "];  // byte offsets of this lane's chunks at k-tile 0\n";
@@ -251,10 +280,16 @@ static std::string phased_loader(const KInfo& ki, const GemmSpec& sp, const std:
   if (sp.M % sp.BM) s << "    r = r < " << sp.M << "LL ? r : " << sp.M - 1 << "LL;\n";
   s << "    va_[i] = (unsigned)((r * " << sp.K << "LL + lk_) * " << eb << ");\n  }\n";
   s << "#pragma unroll\n  for (int i = 0; i < " << PB << "; ++i) {\n";
+  if (sp.bt >= 0) {
+    s << "    i64 r = n0 + " << RB << " * (wv_ + i * " << GW << ") + l / " << CR << ";\n";
+    if (sp.N % sp.BN) s << "    r = r < " << sp.N << "LL ? r : " << sp.N - 1 << "LL;\n";
+    s << "    vb_[i] = (unsigned)((r * " << sp.K << "LL + lk_) * " << eb << ");\n  }\n";
+  } else {
   s << "    const int q = (wv_ + i * " << GW << ") * 64 + l, k = q / " << P << ", p = q % " << P << ";\n";
   s << "    i64 c = n0 + " << b_chunk(sp, "p", "k", true) << " * " << CE << ";\n";
   if (sp.N % sp.BN) s << "    c = c < " << sp.N << "LL ? c : " << sp.N - CE << "LL;\n";
   s << "    vb_[i] = (unsigned)(((i64)k * " << sp.N << "LL + c) * " << eb << ");\n  }\n";
+  }
   auto ld = [&](const char* off, const char* rs) {
     return std::string("      asm volatile(\"s_mov_b32 m0, %1\\n\\ts_nop 0\\n\\tbuffer_load_dwordx4 %0, %2, %3 offen lds\" :: \"v\"(") +
            off + "), \"s\"(la), \"s\"(" + rs + "), \"s\"(so) : \"memory\", \"m0\");\n";
@@ -271,10 +306,12 @@ static std::string phased_loader(const KInfo& ki, const GemmSpec& sp, const std:
   else
     s << ld("va_[i]", "rsA_");
   s << "    }\n    }\n";
-  s << "    {\n    const unsigned so = __builtin_amdgcn_readfirstlane((unsigned)kt * " << eb * sp.BK * sp.N << "u);\n#pragma unroll\n    for (int i = 0; i < " << PB << "; ++i) {\n";
+  s << "    {\n    const unsigned so = __builtin_amdgcn_readfirstlane((unsigned)kt * " << eb * sp.BK * (sp.bt >= 0 ? 1 : sp.N) << "u);\n#pragma unroll\n    for (int i = 0; i < " << PB << "; ++i) {\n";
   if (NB % GW) s << "      if (i == " << PB - 1 << " && wv_ >= " << NB % GW << ") break;  // the first waves load one block more\n";
   s << "      const unsigned la = lds0_ + (unsigned)(" << sp.PST * SAB << " + st * " << SBB << " + (wv_ + i * " << GW << ") * 1024);\n";
-  if (tail)
+  if (tail && sp.bt >= 0)
+    s << "      const unsigned vo = kt == " << KT - 1 << " && lk_ >= " << sp.K % sp.BK << " ? 0x80000000u : vb_[i];\n" << ld("vo", "rsB_");
+  else if (tail)
     s << "      const unsigned vo = kt == " << KT - 1 << " && ((wv_ + i * " << GW << ") * 64 + l) / " << P << " >= " << sp.K % sp.BK
       << " ? 0x80000000u : vb_[i];\n"
       << ld("vo", "rsB_");
@@ -286,6 +323,7 @@ static std::string phased_loader(const KInfo& ki, const GemmSpec& sp, const std:
 
 static std::string phased_mainloop(const GemmSpec& sp, int64_t KTG, bool exact) {
   std::ostringstream s;
+  const int64_t KT = (sp.K + sp.BK - 1) / sp.BK;
   const std::string T = ctype(sp.mtype), V8 = sp.mtype == KORCH_F32 ? "f32x4" : sp.mtype == KORCH_F16 ? "f16x8" : "bf16x8";
   const bool f32 = sp.mtype == KORCH_F32;
   const int eb = dtype_bytes(sp.mtype), CE = 16 / eb, KW = 4 * CE;  // k of one fragment read (four chunks)
@@ -307,6 +345,10 @@ static std::string phased_mainloop(const GemmSpec& sp, int64_t KTG, bool exact) 
   s << "  " << V8 << " fa_[" << NA << "][" << FH << "], fb_[2][" << sp.FN << "];\n";
   s << "  const " << T << "* Af_ = (const " << T << "*)gsm_ + (wm * " << sp.WTM << " + (l & 15)) * " << sp.BK << ";\n";
   s << "  const int ca_ = " << (sp.BK / CE == 8 ? "((l >> 4) ^ (l & 7)) * " : "((l >> 4) ^ ((l >> 1) & 2)) * ") << CE << ";\n";
+  if (sp.bt >= 0) {
+    // rows of the right tile as the left one's
+    s << "  const " << T << "* Bf_ = (const " << T << "*)gsm_ + " << NST * SAE << " + (wn * " << sp.WTN << " + (l & 15)) * " << sp.BK << ";\n";
+  } else {
   s << "  const " << T << "* Bf_ = (const " << T << "*)gsm_ + " << NST * SAE << " + (" << (f32 ? "(l >> 4) * 4" : "(l >> 4) * 8 + ((l & 15) >> 2)") << ") * " << sp.BN << ";\n";
   s << "  int cb_[" << sp.FN << "];\n#pragma unroll\n  for (int j = 0; j < " << sp.FN << "; ++j) {\n";
   if (f32)
@@ -314,6 +356,7 @@ static std::string phased_mainloop(const GemmSpec& sp, int64_t KTG, bool exact) 
   else
     s << "    const int n_ = wn * " << sp.WTN << " + j * 16 + 4 * (l & 3), k_ = (l >> 4) * 8 + ((l & 15) >> 2);\n";
   s << "    cb_[j] = " << b_chunk(sp, "n_ / " + std::to_string(CE), "k_", false) << " * " << CE << " + n_ % " << CE << ";\n  }\n";
+  }
   // left fragments of phase p (rows [p % H * FH, + FH), k-step p / H) of tile t
   // (counted within a round), right fragment j of its k-step kk
   auto setA = [&](int t, int p) { return ((t % U) * NP + p) % NA; };
@@ -327,6 +370,11 @@ static std::string phased_mainloop(const GemmSpec& sp, int64_t KTG, bool exact) 
   };
   auto readB = [&](int t, int kk, int j) {
     std::ostringstream o;
+    if (sp.bt >= 0) {
+      o << "    fb_[" << setB(t, kk) << "][" << j << "] = *(const " << V8 << "*)(Bf_ + " << (t % NST) * SBE + j * 16 * sp.BK << " + (ca_ ^ "
+        << kk * 4 * CE << "));\n";
+      return o.str();
+    }
     if (f32) {
       // the contraction's order is free as long as both fragments agree: lane
       // group g holds the consecutive k 4 g .. 4 g + 3 of the window (one
@@ -351,16 +399,37 @@ static std::string phased_mainloop(const GemmSpec& sp, int64_t KTG, bool exact) 
     if (!n || !PX) return "    " + w(n * PL);
     return "    if (wv_ < " + std::to_string(PX) + ") " + w(n * (PL + 1)) + "    else " + w(n * PL);
   };
+  // Where rows end inside a chunk, the last k-tile's chunk goes on into the next
+  // row: those elements are zeroed in LDS once the tile has landed (index
+  // `last` of the last part; the others pass).  The barrier is every wave's.
+  const int64_t last = exact ? KTG - 1 : std::max<int64_t>(0, KTG - 2);
+  const bool ragged = sp.K % CE != 0;
+  auto trim = [&](int t) {
+    std::ostringstream o;
+    const int64_t kr = sp.K % sp.BK;
+    const int GT = 64 * GW;
+    o << "    if (kt1 == " << KT << ") {\n";
+    for (int op = 0; op < (sp.bt >= 0 ? 2 : 1); ++op) {
+      const int rows = op ? sp.BN : sp.BM;
+      o << "      for (int r_ = tid; r_ < " << rows << "; r_ += " << GT << ") {\n        " << T << "* z_ = (" << T << "*)gsm_ + "
+        << (op ? NST * SAE + (t % NST) * SBE : (t % NST) * SAE) << " + r_ * " << sp.BK << " + (" << kr / CE << " ^ "
+        << (sp.BK / CE == 8 ? "(r_ & 7)" : "((r_ >> 1) & 2)") << ") * " << CE << ";\n#pragma unroll\n        for (int e = " << kr % CE
+        << "; e < " << CE << "; ++e) z_[e] = (" << T << ")0.0f;\n      }\n";
+    }
+    o << "    }\n    __syncthreads();\n";
+    return o.str();
+  };
   // Tile j of the group, number t of a round.  `more`: tile j + NST exists (1)
   // or may exist (2); `next`: tile j + 1 exists; `steady`: tiles j + 2 .. j +
   // NST - 1 exist in every group and are the loads in flight beyond tile j + 1;
   // `live`: the group may have no tile j (a shorter last group).
-  auto tile = [&](const std::string& j, int t, int more, bool next, bool steady, bool live) {
+  auto tile = [&](const std::string& j, int t, int more, bool next, bool steady, bool live, bool trims = false) {
     std::ostringstream o;
     for (int p = 0; p < NP; ++p) {
       if (p == NP - L && next) {
         // tile j + 1 has landed and every wave holds the rest of tile j
         o << wait(steady ? NST - 2 : 0) << "    __syncthreads();\n";
+        if (trims) o << trim(t + 1);
         if (more)
           o << (more == 2 ? "    if (" + j + " + " + std::to_string(NST) + " < nkt_) " : std::string("    ")) << "load_(kt0 + " << j
             << " + " << NST << ", " << t % NST << ");\n";
@@ -403,6 +472,7 @@ static std::string phased_mainloop(const GemmSpec& sp, int64_t KTG, bool exact) 
     s << "  " << (t < KS ? "" : "if (" + std::to_string(t) + " < nkt_) ") << "load_(kt0 + " << t << ", " << t << ");\n";
   // tile 0 landed; the tiles after it may be in flight
   s << wait(KS >= NST ? NST - 1 : 0) << "  __syncthreads();\n";
+  if (ragged && last == 0) s << trim(0);
   for (int p = 0; p < L; ++p) s << readA(0, p);
   s << readBs(0, 0, 0, 1);
   // steady part: tile j + NST exists in every group, in rounds of U tiles
@@ -414,7 +484,8 @@ static std::string phased_mainloop(const GemmSpec& sp, int64_t KTG, bool exact) 
   }
   for (int64_t j = steady; j < KTG; ++j) {
     const int more = j + NST < KS ? 1 : j + NST < KTG ? 2 : 0;
-    s << "  {\n" << tile(std::to_string(j), (int)(j % U), more, j + 1 < KTG, j + NST - 1 < KS, j >= KS) << "  }\n";
+    s << "  {\n" << tile(std::to_string(j), (int)(j % U), more, j + 1 < KTG, j + NST - 1 < KS, j >= KS, ragged && j + 1 == last)
+      << "  }\n";
   }
   if (sp.KSEQ > 1)
     s << "#pragma unroll\n  for (int i = 0; i < " << sp.FM << "; ++i)\n#pragma unroll\n  for (int n = 0; n < " << sp.FN
@@ -423,10 +494,10 @@ static std::string phased_mainloop(const GemmSpec& sp, int64_t KTG, bool exact) 
   return s.str();
 }
 
-GenKernel gen_gemm_phased(const KInfo& ki, GemmSpec& sp, int index) {
+GenKernel gen_gemm_phased(const KInfo& ki, GemmSpec& sp, int index, const char* fam) {
   GenKernel gk;
   gk.family = KORCH_FAM_GEMM;
-  gk.name = kernel_name(index, "gemm");
+  gk.name = kernel_name(index, fam);
   std::map<int, int> slot;
   ki.assign_args(gk, slot);
   const int64_t ntn = (sp.N + sp.BN - 1) / sp.BN, ntm = (sp.M + sp.BM - 1) / sp.BM, KT = (sp.K + sp.BK - 1) / sp.BK;

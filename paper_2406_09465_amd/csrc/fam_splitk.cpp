@@ -260,6 +260,14 @@ GenKernel gen_splitk(const KInfo& ki, int index) {
   SplitInfo si;
   std::string why;
   if (!analyze_splitk(ki, sp, si, &why)) fail(KORCH_E_UNSUPPORTED, why);
+  // a plain skinny product runs the phased main loop (which splits its
+  // contraction over workgroups too, over tiles as wide as the output)
+  plan_operands(ki, sp);
+  if (plan_phased(ki, sp, false)) {
+    GenKernel ph = gen_gemm_phased(ki, sp, index, "splitk");
+    ph.family = KORCH_FAM_SPLITK;
+    return ph;
+  }
   choose_tiles(sp, true);
   plan_operands(ki, sp);
   GenKernel gk;

@@ -70,6 +70,7 @@ struct GemmSpec {
   // Phased main loop (fam_gemm_phased.cpp): groups of WM x WN waves, each over
   // its own part of the k-tiles (0: not taken).
   int KG = 0;
+  int bt = -1;   // stored [.., N, K] tensor that the right operand transposes (-1: stored [.., K, N])
   int PST = 2;   // its stages of each operand
   int KS = 1;    // workgroups that share a tile's contraction
   int KSEQ = 1;  // parts of the contraction summed one after another, then added
@@ -101,7 +102,7 @@ std::string gemm_tile_order(const GemmSpec& sp, int64_t ntm, int64_t ntn, const 
 // Phased main loop: decides (tiles, waves, k-groups) and generates.
 // split_halves: the older path would split the contraction in two inside a workgroup.
 bool plan_phased(const KInfo& ki, GemmSpec& sp, bool split_halves);
-GenKernel gen_gemm_phased(const KInfo& ki, GemmSpec& sp, int index);
+GenKernel gen_gemm_phased(const KInfo& ki, GemmSpec& sp, int index, const char* fam = "gemm");
 
 // LDS element offset of row k of the [k][n] right-operand tile.
 std::string b_row_off(const GemmSpec& sp, const std::string& k);

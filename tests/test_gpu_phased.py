@@ -22,39 +22,42 @@ F32_SHAPES = ["64,128,2,2,1,32,2", "64,96,2,2,1,32,2", "64,64,2,2,1,32,2", "32,6
 # (the last number: the parts of the contraction that workgroups share)
 SPLITS = ["32,64,2,2,2,64,6,2", "32,64,2,2,1,64,6,4", "64,64,2,2,1,64,4,3", "64,96,2,2,2,64,3,5", "128,128,2,4,1,64,4,8"]
 F32_SPLITS = ["32,32,2,2,1,32,4,8", "32,32,2,2,2,32,6,3", "64,64,2,2,1,32,2,5", "32,64,2,2,2,32,6,4"]
-SIZES = [(300, 264, 200), (1, 8, 8), (257, 520, 64), (128, 96, 1000), (33, 72, 456)]
+# rows that end inside a 16-byte chunk among them
+SIZES = [(300, 264, 200), (1, 8, 8), (257, 520, 64), (128, 96, 1000), (33, 72, 456), (130, 74, 322), (65, 2, 62), (40, 130, 2)]
 
 
-def _graph(m, n, k, dtype, epi, batch=0):
+def _graph(m, n, k, dtype, epi, batch=0, bt=False):
     from paper_2406_09465_amd._abi import Graph
     from paper_2406_09465_amd.graphs import Workload
     g = Graph()
     lead = (batch,) if batch else ()
-    ids = {"A": g.input(dtype, lead + (m, k)), "W": g.input(dtype, (k, n))}
+    ids = {"A": g.input(dtype, lead + (m, k)), "W": g.input(dtype, ((batch,) if bt and batch else ()) + ((n, k) if bt else (k, n)))}
     names = ["A", "W"]
     if epi == "residual":
         ids["R"] = g.input(dtype, lead + (m, n))
         names.append("R")
-    if batch:  # a right operand shared by the batch
+    if bt:  # the right operand is a transpose inside the kernel
+        ids["Wb"] = g.op("transpose", [ids["W"]], dtype, perm=(0, 2, 1) if batch else (1, 0))
+    elif batch:  # a right operand shared by the batch
         ids["Wb"] = g.op("reshape", [ids["W"]], dtype, shape=(1, k, n))
-    ids["C"] = g.op("matmul", [ids["A"], ids["Wb" if batch else "W"]], dtype)
+    ids["C"] = g.op("matmul", [ids["A"], ids["Wb" if batch or bt else "W"]], dtype)
     ids["out"] = ids["C"]
-    prims = ([ids["Wb"]] if batch else []) + [ids["C"]]
+    prims = ([ids["Wb"]] if bt else []) + [ids["C"]]
     if epi == "residual":
         ids["out"] = g.op("add", [ids["C"], ids["R"]], dtype)
         prims.append(ids["out"])
     g.output(ids["out"])
     g.finalize()
-    return Workload("product", dtype, g, ids, names, ["out"]), [([p for p in prims if p != ids.get("Wb")], [ids["out"]])]
+    return Workload("product", dtype, g, ids, names, ["out"]), [(prims, [ids["out"]])]
 
 
-def _run(m, n, k, dtype, epi, batch=0, edit=None, seed=0):
+def _run(m, n, k, dtype, epi, batch=0, edit=None, seed=0, bt=False):
     from paper_2406_09465_amd.runner import TORCH_DTYPE, PlanRunner
-    w, kernels = _graph(m, n, k, dtype, epi, batch)
+    w, kernels = _graph(m, n, k, dtype, epi, batch, bt)
     r = PlanRunner(w, kernels=kernels)
     gen = torch.Generator(device="cuda").manual_seed(seed)
     lead = (batch,) if batch else ()
-    shapes = {"A": lead + (m, k), "W": (k, n), "R": lead + (m, n)}
+    shapes = {"A": lead + (m, k), "W": (lead if bt else ()) + ((n, k) if bt else (k, n)), "R": lead + (m, n)}
     x = {nm: torch.randn(shapes[nm], generator=gen, device="cuda").to(TORCH_DTYPE[dtype]) for nm in w.input_names}
     if edit:
         edit(x)
@@ -62,7 +65,10 @@ def _run(m, n, k, dtype, epi, batch=0, edit=None, seed=0):
     r.bind()
     r.launch_bound()
     torch.cuda.synchronize()
-    return r, {nm: v.double().cpu() for nm, v in x.items()}
+    x = {nm: v.double().cpu() for nm, v in x.items()}
+    if bt:
+        x["W"] = x["W"].transpose(-1, -2).contiguous()
+    return r, x
 
 
 def _check(r, x, k, dtype):
@@ -128,7 +134,7 @@ def test_workgroup_splits_keep_plans_allocation_free():
 
 
 def test_phased_selection():
-    """Plain products take the path; rows that are not 16-byte chunks and small
+    """Plain products take the path; rows that do not start on dwords and small
     short 16-bit products do not."""
     from paper_2406_09465_amd._abi import Plan
 
@@ -138,8 +144,8 @@ def test_phased_selection():
         return "offen lds" in p.kernel_source(0)
 
     assert phased(4096, 1024, 1024, "bf16") and phased(1576, 384, 1536, "f16") and phased(301, 264, 1000, "f16")
-    assert phased(2048, 768, 3072, "f32") and phased(49, 100, 36, "f32") and not phased(512, 512, 510, "f32")
-    assert not phased(4096, 1024, 1020, "f16") and not phased(512, 512, 128, "f16")
+    assert phased(2048, 768, 3072, "f32") and phased(49, 101, 37, "f32") and phased(512, 510, 1022, "bf16")
+    assert not phased(4096, 1024, 1021, "f16") and not phased(4096, 1023, 1024, "f16") and not phased(512, 512, 128, "f16")
 
 
 @pytest.mark.gpu
@@ -150,9 +156,9 @@ def test_phased_product(cfg, size, monkeypatch):
         pytest.skip("no GPU")
     monkeypatch.setenv("KORCH_GEMM_PHASED", cfg)
     m, n, k = size
-    for dtype, epi, batch in (("f16", "", 0), ("bf16", "residual", 0), ("f16", "residual", 3)):
-        print(f"\n[case] phased {cfg} {size} {dtype} {epi} batch {batch}", flush=True)
-        r, x = _run(m, n, k, dtype, epi, batch, seed=m + n + k)
+    for dtype, epi, batch, bt in (("f16", "", 0, False), ("bf16", "residual", 0, True), ("f16", "residual", 3, False)):
+        print(f"\n[case] phased {cfg} {size} {dtype} {epi} batch {batch} bt {bt}", flush=True)
+        r, x = _run(m, n, k, dtype, epi, batch, seed=m + n + k, bt=bt)
         assert "offen lds" in r.plan.kernel_source(0)
         _check(r, x, k, dtype)
         first = r.outs[0].clone()
@@ -163,7 +169,8 @@ def test_phased_product(cfg, size, monkeypatch):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("size", [(300, 264, 200), (1, 4, 4), (129, 100, 36), (70, 96, 1000), (33, 68, 452)],
+@pytest.mark.parametrize("size", [(300, 264, 200), (1, 4, 4), (129, 100, 36), (70, 96, 1000), (33, 68, 452), (65, 33, 97), (50, 1, 1),
+                                  (34, 71, 191)],
                          ids=lambda s: "x".join(map(str, s)))
 @pytest.mark.parametrize("cfg", F32_SHAPES + F32_SPLITS)
 def test_phased_f32_product(cfg, size, monkeypatch):
@@ -171,9 +178,9 @@ def test_phased_f32_product(cfg, size, monkeypatch):
         pytest.skip("no GPU")
     monkeypatch.setenv("KORCH_GEMM_PHASED", cfg)
     m, n, k = size
-    for epi, batch in (("", 0), ("residual", 3)):
-        print(f"\n[case] phased f32 {cfg} {size} {epi} batch {batch}", flush=True)
-        r, x = _run(m, n, k, "f32", epi, batch, seed=m + n + k)
+    for epi, batch, bt in (("", 0, True), ("residual", 3, False), ("", 2, True)):
+        print(f"\n[case] phased f32 {cfg} {size} {epi} batch {batch} bt {bt}", flush=True)
+        r, x = _run(m, n, k, "f32", epi, batch, seed=m + n + k, bt=bt)
         assert "offen lds" in r.plan.kernel_source(0)
         _check(r, x, k, "f32")
         first = r.outs[0].clone()
@@ -210,8 +217,16 @@ def test_phased_nonfinite_rows_stay_apart():
         x["A"][3::4, 7] = float("nan")
 
     print("\n[case] phased nonfinite", flush=True)
-    r, x = _run(130, 136, 1000, "f16", "", edit=edit)
+    for k in (1000, 1002, 998):  # the last two end inside a chunk
+        r, x = _run(130, 136, k, "f16", "", edit=edit)
+        out = r.outs[0].double().cpu()
+        ref = x["A"][0::2] @ x["W"]
+        assert bool(torch.isfinite(out[0::2]).all()) and np.allclose(out[0::2], ref, rtol=2e-3, atol=0.15)
+        assert not bool(torch.isfinite(out[1::2]).any())
+
+    def edit_w(x):  # rows of the transposed operand
+        x["W"][1::2] = float("nan")
+
+    r, x = _run(70, 136, 37, "f32", "", edit=edit_w, bt=True)
     out = r.outs[0].double().cpu()
-    ref = x["A"][0::2] @ x["W"]
-    assert bool(torch.isfinite(out[0::2]).all()) and np.allclose(out[0::2], ref, rtol=2e-3, atol=0.15)
-    assert not bool(torch.isfinite(out[1::2]).any())
+    assert np.allclose(out[:, 0::2], x["A"] @ x["W"][:, 0::2], rtol=1e-5, atol=1e-4) and bool(torch.isnan(out[:, 1::2]).all())
