@@ -35,6 +35,7 @@ struct GenKernel {
   int lds_bytes = 0;  // static LDS (informational)
   std::vector<ArgRef> args;
   double alg_bytes = 0, alg_flops = 0;
+  bool wg_split = false;  // a product's contraction is split over workgroups
 };
 
 // Family matcher only (no source); returns the family or KORCH_FAM_NONE with a reason.

@@ -70,7 +70,7 @@ static void generate_kernels(Plan& p) {
 void generate_plan(Plan& p) {
   if (!p.ck.empty()) return;
   generate_kernels(p);
-  if (fits_static_scratch(p)) return;
+  if (fits_static_scratch(p) || std::none_of(p.ck.begin(), p.ck.end(), [](const CompiledKernel& c) { return c.gen.wg_split; })) return;
   p.wg_splits = false;
   generate_kernels(p);
   if (fits_static_scratch(p)) return;

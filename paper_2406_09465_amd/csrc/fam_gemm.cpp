@@ -1749,7 +1749,7 @@ std::string gemm_epilogue(const KInfo& ki, const GemmSpec& sp, const std::map<in
   // the compiler then issues all of a thread's loads before the first is used
   // (a runtime-bounded loop loads, waits and stores one vector at a time).
   const int nvec_ = rows * (cols / VE);
-  if (conv_tw <= 0 && sp.M % sp.BM == 0 && n_full && nvec_ % sp.NT == 0 && nvec_ / sp.NT <= 8 &&
+  if (conv_tw <= 0 && !sp.conv && sp.M % sp.BM == 0 && n_full && nvec_ % sp.NT == 0 && nvec_ / sp.NT <= 8 &&
       em.n_vector + em.n_gather > 0) {
     // Every thread stores nvec_ / NT vectors and none is guarded: the loads of
     // all of them (C tile and tensors read per element) are written out first,
@@ -1878,7 +1878,11 @@ GenKernel gen_gemm(const KInfo& ki, int index) {
   plan_operands(ki, sp);
   {
     const int64_t kt = (sp.K + sp.BK - 1) / sp.BK, tiles = (sp.M + sp.BM - 1) / sp.BM * ((sp.N + sp.BN - 1) / sp.BN) * sp.batch;
-    if (plan_phased(ki, sp, sp.mms.size() == 1 && sp.NT == 256 && tiles <= 256 && kt >= 16)) return gen_gemm_phased(ki, sp, index);
+    if (plan_phased(ki, sp, !sp.conv && sp.mms.size() == 1 && sp.NT == 256 && tiles <= 256 && kt >= 16)) {
+      GenKernel ph = gen_gemm_phased(ki, sp, index, sp.conv ? "conv" : "gemm");
+      if (sp.conv) ph.family = KORCH_FAM_CONV;
+      return ph;
+    }
   }
   if ((sp.K + sp.BK - 1) / sp.BK > 128) sp.NS = 2;  // long contractions use the rolled loop
   if (sp.WM > 1 && !getenv("KORCH_GEMM_FULL_CTILE")) sp.CROWS = sp.WTM;

@@ -122,6 +122,10 @@ static bool phased_tiles(GemmSpec& sp) {
     return true;
   }
   for (const Shape_& h : shapes) {
+    // 96 columns do not divide the threads: a convolution's per-channel operands
+    // would be loaded for every element (275 x 129, 64 to 256 channels, 1 x 1:
+    // 13.9 us in 128 x 96 tiles, 11.6 in 128 x 128)
+    if (h.bn == 96 && sp.conv) continue;
     const int64_t tiles = (sp.M + h.bm - 1) / h.bm * ((sp.N + h.bn - 1) / h.bn) * sp.batch;
     const int64_t full = tiles / (256 * h.c), rest = (tiles - full * 256 * h.c + 255) / 256;
     const double tr = h.c > 1 ? h.t1 + (h.tc - h.t1) * (double)(rest - 1) / (h.c - 1) : h.t1;
@@ -179,27 +183,43 @@ bool plan_phased(const KInfo& ki, GemmSpec& sp, bool split_halves) {
                         "KORCH_GEMM_DMA_KSPLIT", "KORCH_GEMM_DMA_2STAGE", "KORCH_GEMM_DMA_A3", "KORCH_GEMM_DMA_STAGES",
                         "KORCH_GEMM_SPLIT_STEPS"})
     if (env_set(n)) return false;
-  if (sp.conv || sp.lnf || sp.mms.size() != 1 || sp.Bs.size() != 1 || !sp.side.empty() || !sp.rowred.empty()) return false;
+  if (sp.lnf || sp.mms.size() != 1 || sp.Bs.size() != 1 || !sp.side.empty() || !sp.rowred.empty()) return false;
   const int eb = dtype_bytes(sp.mtype), CE = 16 / eb;
   if (ki.in.count(sp.A)) return false;  // operands computed in the kernel
   const int bt = ki.in.count(sp.Bs[0]) ? transposed_source(ki, sp) : -1;
   if (ki.in.count(sp.Bs[0]) && bt < 0) return false;
   // rows start on whole dwords (what a load to LDS needs; 16 bytes are read from any)
+  if (sp.conv) {
+    // implicit GEMM: a k-tile lies within one filter tap, so its left rows are
+    // pixels at one shift (weights [KH, KW, Cin, Cout] are a [K, N] matrix)
+    if (bt >= 0 || sp.nb || sp.Cin % (4 * CE) || (double)sp.H * sp.W * sp.Cin * eb >= 2147483648.0) return false;
+  }
   if (sp.K * eb % 4 || (bt < 0 && sp.N * eb % 4)) return false;
   // buffer loads: byte offsets below 2 GiB from a batch's operand
   if ((double)sp.M * sp.K * eb >= 2147483648.0 || (double)sp.K * sp.N * eb >= 2147483648.0) return false;
   // Products that 192-wide tiles divide into whole rounds keep those tiles and
   // their own staging (4096 x 3072 x 768 with a GELU: 22.9 us, phased 22.4).
-  if (!getenv("KORCH_GEMM_PHASED") && sp.BN == 192) return false;
+  if (!getenv("KORCH_GEMM_PHASED") && sp.BN == 192 && !sp.conv) return false;
   // So do small products of up to four k-tiles whose tiles divide them: there is
   // nothing to pipeline (1024 x 768 x 256: 3.8 us, phased 3.9; 16384 x 64 x 256:
   // 3.7 either way; 4096 x 1024 x 256, above the line: 6.7 and 6.0).
-  if (!getenv("KORCH_GEMM_PHASED") && sp.M * sp.N * sp.batch <= 1 << 20 && sp.K <= 256 && sp.K % 64 == 0 && sp.M % sp.BM == 0 &&
+  if (!getenv("KORCH_GEMM_PHASED") && !sp.conv && sp.M * sp.N * sp.batch <= 1 << 20 && sp.K <= 256 && sp.K % 64 == 0 && sp.M % sp.BM == 0 &&
       sp.N % sp.BN == 0)
     return false;
+  // Outputs of 16 columns waste half of the narrowest tile: a short convolution
+  // to them keeps its own (300 x 300, 256 to 16 channels: 10.9 us, phased 12.6;
+  // 141 x 141 with 3 x 3 taps of 128 channels, above the line: 9.5 and 8.9).
+  if (!getenv("KORCH_GEMM_PHASED") && sp.conv && sp.N <= 16 && sp.K <= 256) return false;
+  // So does one over many pixels whose three or four k-tiles are of 32 channels
+  // (275 x 129, 96 to 256 channels, 1 x 1: 11.0 us, phased 12.4).
+  if (!getenv("KORCH_GEMM_PHASED") && sp.conv && CE == 8 && sp.Cin % 64 && sp.K <= 128 && sp.M * sp.N >= 1 << 22) return false;
+  // fp32 outputs stored float by float after one k-tile: the stores are the time
+  // (1477 x 1477 x 16: 4.7 us, phased 6.8; with K = 96, 1799 x 1799: 15.4 and 13.0).
+  if (!getenv("KORCH_GEMM_PHASED") && CE == 4 && sp.N % 4 && sp.K <= 32) return false;
   GemmSpec t = sp;
   t.bt = bt;
   if (!phased_tiles(t)) return false;
+  if (t.conv && t.Cin % t.BK) t.BK /= 2, t.PST = std::min(12, 2 * t.PST);  // the same LDS in twice the stages
   if (t.KS < 1 || t.KS * t.KG > (t.K + t.BK - 1) / t.BK) t.KS = 1;
   // A long contraction whose 128-row tiles leave at most one per compute unit
   // is summed in two halves that are added at the end, as its k-split kernel
@@ -266,19 +286,25 @@ static std::string phased_loader(const KInfo& ki, const GemmSpec& sp, const std:
   s << "  typedef int i32x4_ __attribute__((ext_vector_type(4)));\n";
   auto rsrc = [&](const char* X, int node, int64_t bytes) {
     s << "  const size_t p" << X << "_ = (size_t)((const " << T << "*)a.p[" << slot.at(node) << "] + ("
-      << operand_batch_offset(ki, sp, node) << "));\n";
+      << (sp.conv ? std::string("0") : operand_batch_offset(ki, sp, node)) << "));\n";
     s << "  const i32x4_ rs" << X << "_ = {__builtin_amdgcn_readfirstlane((int)(unsigned)p" << X
       << "_), __builtin_amdgcn_readfirstlane((int)((p" << X << "_ >> 32) & 0xffff)), " << (long long)bytes << ", 0x00020000};\n";
   };
-  rsrc("A", sp.A, sp.M * sp.K * eb);
+  rsrc("A", sp.A, (sp.conv ? sp.H * sp.W * sp.Cin : sp.M * sp.K) * eb);
   rsrc("B", sp.bt >= 0 ? sp.bt : sp.Bs[0], sp.K * sp.N * eb);
   // k of this lane's left chunk within a tile (its position holds chunk c ^ g(row))
   s << "  const int lk_ = " << (CR == 8 ? "((l & 7) ^ (l >> 3)) * " : "((l & 3) ^ ((l >> 3) & 2)) * ") << CE << ";\n";
   s << "  unsigned va_[" << PA << "], vb_[" << PB << "];  // byte offsets of this lane's chunks at k-tile 0\n";
+  if (sp.conv) s << "  int py_[" << PA << "], px_[" << PA << "];  // input pixel under the filter's first tap\n";
   s << "#pragma unroll\n  for (int i = 0; i < " << PA << "; ++i) {\n";
   s << "    i64 r = m0 + " << RB << " * (wv_ + i * " << GW << ") + l / " << CR << ";\n";
   if (sp.M % sp.BM) s << "    r = r < " << sp.M << "LL ? r : " << sp.M - 1 << "LL;\n";
-  s << "    va_[i] = (unsigned)((r * " << sp.K << "LL + lk_) * " << eb << ");\n  }\n";
+  if (sp.conv)
+    s << "    py_[i] = (int)r / " << sp.Wo << " * " << sp.stride << " - " << sp.pad << ";\n    px_[i] = (int)r % " << sp.Wo << " * " << sp.stride
+      << " - " << sp.pad << ";\n    va_[i] = (unsigned)(((py_[i] * " << sp.W << " + px_[i]) * " << sp.Cin << " + lk_) * " << eb << ");\n  }\n";
+  else
+    s << "    va_[i] = (unsigned)((r * " << sp.K << "LL + lk_) * " << eb << ");\n  }\n";
+
   s << "#pragma unroll\n  for (int i = 0; i < " << PB << "; ++i) {\n";
   if (sp.bt >= 0) {
     s << "    i64 r = n0 + " << RB << " * (wv_ + i * " << GW << ") + l / " << CR << ";\n";
@@ -297,9 +323,20 @@ static std::string phased_loader(const KInfo& ki, const GemmSpec& sp, const std:
   const bool tail = sp.K % sp.BK != 0;
   // tile kt into stage st
   s << "  auto load_ = [&](const int kt, const int st) {\n";
-  s << "    {\n    const unsigned so = __builtin_amdgcn_readfirstlane((unsigned)kt * " << sp.BK * eb << "u);\n#pragma unroll\n    for (int i = 0; i < " << PA << "; ++i) {\n";
+  if (sp.conv) {
+    // the tile's tap (ky, kx) and channels: a uniform shift of every pixel; taps
+    // outside the image read zero (an offset past the buffer)
+    s << "    const int tap_ = kt * " << sp.BK << " / " << sp.Cin << ", ky_ = tap_ / " << sp.KW << ", kx_ = tap_ % " << sp.KW << ";\n";
+    s << "    const unsigned to_ = (unsigned)(((ky_ * " << sp.W << " + kx_) * " << sp.Cin << " + kt * " << sp.BK << " % " << sp.Cin << ") * "
+      << eb << ");\n";
+  }
+  s << "    {\n    const unsigned so = __builtin_amdgcn_readfirstlane(" << (sp.conv ? "0u * " : "") << "(unsigned)kt * " << sp.BK * eb << "u);\n#pragma unroll\n    for (int i = 0; i < " << PA << "; ++i) {\n";
   s << "      const unsigned la = lds0_ + (unsigned)(st * " << SAB << " + (wv_ + i * " << GW << ") * 1024);\n";
-  if (tail)
+  if (sp.conv)
+    s << "      const unsigned vo = (unsigned)(py_[i] + ky_) < " << sp.H << "u && (unsigned)(px_[i] + kx_) < " << sp.W
+      << "u ? va_[i] + to_ : 0x80000000u;\n"
+      << ld("vo", "rsA_");
+  else if (tail)
     s << "      const unsigned vo = kt == " << KT - 1 << " && lk_ >= " << sp.K % sp.BK
       << " ? 0x80000000u : va_[i];\n"
       << ld("vo", "rsA_");
@@ -441,20 +478,16 @@ static std::string phased_mainloop(const GemmSpec& sp, int64_t KTG, bool exact) 
         if (p / H == kk - 1) o << readBs(t, kk, p % H, H);
       if (p >= NP - L && next) o << readBs(t + 1, 0, p - (NP - L), L);
       o << (live ? "    if (" + j + " < nkt_) {\n" : "    {\n");
-      const int h = p % H;
-      for (int i = 0; i < FH; ++i)
-        for (int n = 0; n < sp.FN; ++n) {
-          const std::string A = "fa_[" + std::to_string(setA(t, p)) + "][" + std::to_string(i) + "]",
-                            B = "fb_[" + std::to_string(setB(t, p / H)) + "][" + std::to_string(n) + "]",
-                            C = "acc[" + std::to_string(h * FH + i) + "][" + std::to_string(n) + "]";
-          if (f32) {
-            for (int q = 0; q < 4; ++q)
-              o << "      " << C << " = __builtin_amdgcn_mfma_f32_16x16x4f32(" << A << "[" << q << "], " << B << "[" << q << "], " << C
-                << ", 0, 0, 0);\n";
-            continue;
-          }
-          o << "      " << C << " = " << fn << "(" << (sp.acc_t ? B + ", " + A : A + ", " + B) << ", " << C << ", 0, 0, 0);\n";
-        }
+      const std::string A = "fa_[" + std::to_string(setA(t, p)) + "][i]", B = "fb_[" + std::to_string(setB(t, p / H)) + "][n]",
+                        C = "acc[" + std::to_string((p % H) * FH) + " + i][n]";
+      o << "#pragma unroll\n      for (int i = 0; i < " << FH << "; ++i)\n#pragma unroll\n        for (int n = 0; n < " << sp.FN << "; ++n) {\n";
+      if (f32)
+        for (int q = 0; q < 4; ++q)
+          o << "          " << C << " = __builtin_amdgcn_mfma_f32_16x16x4f32(" << A << "[" << q << "], " << B << "[" << q << "], " << C
+            << ", 0, 0, 0);\n";
+      else
+        o << "          " << C << " = " << fn << "(" << (sp.acc_t ? B + ", " + A : A + ", " + B) << ", " << C << ", 0, 0, 0);\n";
+      o << "        }\n";
       o << "    }\n    __builtin_amdgcn_sched_barrier(0);\n";
     }
     if (sp.KSEQ > 1) {
@@ -509,6 +542,7 @@ GenKernel gen_gemm_phased(const KInfo& ki, GemmSpec& sp, int index, const char* 
   // order and runs the epilogue.  One counter per tile on a line of its own.
   const size_t part_bytes = (size_t)sp.BM * sp.BN * 4;
   int scr_slot = -1, cnt_slot = -1;
+  gk.wg_split = sp.KS > 1;
   if (sp.KS > 1) {
     ArgRef scr;
     scr.kind = ArgRef::Scratch;
@@ -620,13 +654,22 @@ GenKernel gen_gemm_phased(const KInfo& ki, GemmSpec& sp, int index, const char* 
     // the later ones are still in registers, with one barrier per band.
     const int FQ = phased_band(sp), NQ = sp.FM / FQ, R = 16 * FQ, rows = sp.WM * R;
     s << "  float* Cs = (float*)smem;\n";
+    std::string inv;  // loads that are the same for every element of a thread, once before the bands
+    // one band's code, its row offsets left open (QROW_, QOFF_)
+    const std::string band = gemm_epilogue(ki, sp, slot, "(QROW_ + mlc) * " + std::to_string(sp.LDC), {}, 0, rows,
+                                           "(mlc / " + std::to_string(R) + ") * " + std::to_string(sp.WTM - R) + " + QOFF_", &inv);
+    auto filled = [](std::string t, const std::string& from, int64_t v) {
+      const std::string to = std::to_string(v);
+      for (size_t i = t.find(from); i != std::string::npos; i = t.find(from, i + to.size())) t.replace(i, from.size(), to);
+      return t;
+    };
+    s << inv;
     for (int q = 0; q < NQ; ++q) {
       s << "  {\n#pragma unroll\n  for (int i = 0; i < " << FQ << "; ++i)\n#pragma unroll\n  for (int j = 0; j < " << sp.FN
         << "; ++j)\n#pragma unroll\n  for (int r = 0; r < 4; ++r) Cs[(" << (q & 1) * rows << " + wm * " << R
         << " + i * 16 + (l >> 4) * 4 + r) * " << sp.LDC << " + wn * " << sp.WTN << " + j * 16 + (l & 15)] = acc[" << q * FQ
         << " + i][j][r];\n  }\n  __syncthreads();\n";
-      s << gemm_epilogue(ki, sp, slot, "(" + std::to_string((q & 1) * rows) + " + mlc) * " + std::to_string(sp.LDC), {}, 0, rows,
-                         "(mlc / " + std::to_string(R) + ") * " + std::to_string(sp.WTM - R) + " + " + std::to_string(q * R));
+      s << filled(filled(band, "QROW_", (q & 1) * rows), "QOFF_", q * R);
     }
   }
   s << "  }\n}\n";

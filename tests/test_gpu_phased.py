@@ -35,7 +35,8 @@ def _graph(m, n, k, dtype, epi, batch=0, bt=False):
     names = ["A", "W"]
     if epi == "residual":
         ids["R"] = g.input(dtype, lead + (m, n))
-        names.append("R")
+        ids["b"] = g.input(dtype, (n,))
+        names += ["R", "b"]
     if bt:  # the right operand is a transpose inside the kernel
         ids["Wb"] = g.op("transpose", [ids["W"]], dtype, perm=(0, 2, 1) if batch else (1, 0))
     elif batch:  # a right operand shared by the batch
@@ -43,9 +44,10 @@ def _graph(m, n, k, dtype, epi, batch=0, bt=False):
     ids["C"] = g.op("matmul", [ids["A"], ids["Wb" if batch or bt else "W"]], dtype)
     ids["out"] = ids["C"]
     prims = ([ids["Wb"]] if bt else []) + [ids["C"]]
-    if epi == "residual":
-        ids["out"] = g.op("add", [ids["C"], ids["R"]], dtype)
-        prims.append(ids["out"])
+    if epi == "residual":  # a value per column and one per element
+        ids["Cb"] = g.op("add", [ids["C"], ids["b"]], dtype)
+        ids["out"] = g.op("add", [ids["Cb"], ids["R"]], dtype)
+        prims += [ids["Cb"], ids["out"]]
     g.output(ids["out"])
     g.finalize()
     return Workload("product", dtype, g, ids, names, ["out"]), [(prims, [ids["out"]])]
@@ -57,7 +59,7 @@ def _run(m, n, k, dtype, epi, batch=0, edit=None, seed=0, bt=False):
     r = PlanRunner(w, kernels=kernels)
     gen = torch.Generator(device="cuda").manual_seed(seed)
     lead = (batch,) if batch else ()
-    shapes = {"A": lead + (m, k), "W": (lead if bt else ()) + ((n, k) if bt else (k, n)), "R": lead + (m, n)}
+    shapes = {"A": lead + (m, k), "W": (lead if bt else ()) + ((n, k) if bt else (k, n)), "R": lead + (m, n), "b": (n,)}
     x = {nm: torch.randn(shapes[nm], generator=gen, device="cuda").to(TORCH_DTYPE[dtype]) for nm in w.input_names}
     if edit:
         edit(x)
@@ -76,10 +78,10 @@ def _check(r, x, k, dtype):
     ref = x["A"] @ x["W"]
     mag = x["A"].abs() @ x["W"].abs()
     if "R" in x:
-        ref = ref + x["R"]
-        mag = mag + x["R"].abs()
+        ref = ref + x["b"] + x["R"]
+        mag = mag + x["b"].abs() + x["R"].abs()
     eps = {"f16": 2.0 ** -11, "bf16": 2.0 ** -8, "f32": 2.0 ** -24}[dtype]
-    bound = eps * ref.abs() * 1.01 + (k + 2) * 2.0 ** -24 * mag + 2.0 ** -24
+    bound = eps * ref.abs() * 1.01 + (k + 3) * 2.0 ** -24 * mag + 2.0 ** -24
     bad = (out - ref).abs() > bound
     assert not bool(bad.any()), f"{int(bad.sum())} of {bad.numel()} beyond the bound, worst {float(((out - ref).abs() / bound).max()):.2f}"
 
@@ -230,3 +232,32 @@ def test_phased_nonfinite_rows_stay_apart():
     r, x = _run(70, 136, 37, "f32", "", edit=edit_w, bt=True)
     out = r.outs[0].double().cpu()
     assert np.allclose(out[:, 0::2], x["A"] @ x["W"][:, 0::2], rtol=1e-5, atol=1e-4) and bool(torch.isnan(out[:, 1::2]).all())
+
+
+# Convolutions that the direct kernel does not take, as implicit GEMMs of the
+# phased loop: k-tiles of 64 and of 32 channels, every filter size, images
+# smaller than a tile, more workgroups than pixels, a per-channel epilogue.
+CONVS = [("f16", 52, 52, 128, 256, 3), ("bf16", 9, 7, 256, 48, 5), ("f16", 33, 130, 96, 256, 3), ("f32", 31, 17, 64, 40, 3),
+         ("bf16", 64, 64, 192, 96, 1), ("f32", 20, 20, 32, 256, 5), ("f16", 100, 100, 160, 128, 3)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", CONVS, ids=lambda c: "x".join(map(str, c)))
+def test_phased_convolution(case):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from oracle import configs as OC
+    from oracle.graph import run_unfused
+    from paper_2406_09465_amd import graphs
+    from paper_2406_09465_amd.runner import PlanRunner
+    from tests.helpers import TOL, close, inputs_f64
+    dtype, hh, ww, cin, cout, k = case
+    print(f"\n[case] phased conv {case}", flush=True)
+    sizes = dict(hh=hh, ww=ww, cin=cin, cout=cout, k=k)
+    raw, x = inputs_f64("conv", dtype=dtype, **sizes)
+    ref = run_unfused(OC.build("conv", **sizes), x)
+    r = PlanRunner(graphs.build("conv", dtype=dtype, **sizes), "fused")
+    assert "offen lds" in r.plan.kernel_source(0)
+    out = r.run(raw)
+    ok, mx, rel = close(out["Y"], ref["Y"], TOL[dtype])
+    assert ok, f"max abs err {mx:.3e}, normwise rel {rel:.3e}"
