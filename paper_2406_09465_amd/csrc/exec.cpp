@@ -66,11 +66,13 @@ static void generate_kernels(Plan& p) {
 }
 
 // The splits' scratch and counters must not keep a plan out of allocation-free
-// execution: a plan that only fits the static scratch without them has none.
+// execution: a plan that only fits the static scratch without them has none
+// (one that splits nothing is generated once, whatever it needs).
 void generate_plan(Plan& p) {
   if (!p.ck.empty()) return;
   generate_kernels(p);
-  if (fits_static_scratch(p) || std::none_of(p.ck.begin(), p.ck.end(), [](const CompiledKernel& c) { return c.gen.wg_split; })) return;
+  const bool split = std::any_of(p.ck.begin(), p.ck.end(), [](const CompiledKernel& c) { return c.gen.wg_split; });
+  if (!split || fits_static_scratch(p)) return;
   p.wg_splits = false;
   generate_kernels(p);
   if (fits_static_scratch(p)) return;

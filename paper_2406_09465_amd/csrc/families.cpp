@@ -609,7 +609,7 @@ bool match_colreduce(const KInfo& ki, std::string* why) {
 // Golub and LeVeque's pairwise formula
 //   n = na + nb,  mean = ma + (mb - ma) nb / n,  M2 = M2a + M2b + (mb - ma)^2 na nb / n,
 // always with the lower lane, wave or split as a, in a fixed order (lanes by
-// butterflies, then the four waves, then the splits' partials in split
+// butterflies, then the waves, then the splits' partials in split
 // order), so results are deterministic.  The mean m and v = M2 / L are what
 // the graph's two means compute (up to rounding); X is read once.
 static GenKernel gen_colmoments(const KInfo& ki, int index, const Moments& mo) {
