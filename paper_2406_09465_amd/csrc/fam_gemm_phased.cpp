@@ -126,6 +126,11 @@ static bool phased_tiles(GemmSpec& sp) {
     // would be loaded for every element (275 x 129, 64 to 256 channels, 1 x 1:
     // 13.9 us in 128 x 96 tiles, 11.6 in 128 x 128)
     if (h.bn == 96 && sp.conv) continue;
+    // register relief 1: no 256 x 256 tiles (128 accumulators beside the loads of
+    // an epilogue with three operands of the output's shape spill 17 registers;
+    // 16384 x 4096 x 1024 with it takes 203 us in 256 x 128 tiles, 247 with
+    // 128-row tiles staged through registers)
+    if (h.bm * h.bn == 256 * 256 && reg_relief() >= 1) continue;
     const int64_t tiles = (sp.M + h.bm - 1) / h.bm * ((sp.N + h.bn - 1) / h.bn) * sp.batch;
     const int64_t full = tiles / (256 * h.c), rest = (tiles - full * 256 * h.c + 255) / 256;
     const double tr = h.c > 1 ? h.t1 + (h.tc - h.t1) * (double)(rest - 1) / (h.c - 1) : h.t1;
@@ -183,6 +188,7 @@ bool plan_phased(const KInfo& ki, GemmSpec& sp, bool split_halves) {
                         "KORCH_GEMM_DMA_KSPLIT", "KORCH_GEMM_DMA_2STAGE", "KORCH_GEMM_DMA_A3", "KORCH_GEMM_DMA_STAGES",
                         "KORCH_GEMM_SPLIT_STEPS"})
     if (env_set(n)) return false;
+  if (reg_relief() >= 2) return false;
   if (sp.lnf || sp.mms.size() != 1 || sp.Bs.size() != 1 || !sp.side.empty() || !sp.rowred.empty()) return false;
   const int eb = dtype_bytes(sp.mtype), CE = 16 / eb;
   if (ki.in.count(sp.A)) return false;  // operands computed in the kernel

@@ -120,6 +120,26 @@ def test_phased_kernels_compile_without_spills(cfg, monkeypatch):
         assert m0 and all(ins[i][:2] == ["s_mov_b32", "m0,"] and ins[i + 1][0] == "s_nop" and ins[i + 2][-1] == "lds" for i in m0)
 
 
+def test_phased_epilogue_that_spills_takes_smaller_tiles():
+    """Three operands of the output's shape spill beside the accumulators of 256 x
+    256 tiles; the kernel is generated again with 256 x 128."""
+    from paper_2406_09465_amd import codeobj
+    from paper_2406_09465_amd._abi import Graph, Plan
+    g = Graph()
+    a, b = g.input("bf16", (16384, 1024)), g.input("bf16", (1024, 4096))
+    rest = [g.input("bf16", (16384, 4096)) for _ in range(3)] + [g.input("bf16", (4096,)) for _ in range(3)]
+    prims = [g.op("matmul", [a, b], "bf16")]
+    for i, r in enumerate(rest[3:] + rest[:3]):
+        prims.append(g.op("add" if i < 3 else "mul", [prims[-1], r], "bf16"))
+    g.output(prims[-1])
+    g.finalize()
+    p = Plan(g, [(prims, [prims[-1]])])
+    p.compile()
+    (res,) = codeobj.kernel_resources(p.kernel_code(0)).values()
+    assert res["scratch"] == 0 and "offen lds" in p.kernel_source(0)
+    assert p.kernel_launch(0)[0][0] == 16384 // 256 * 4096 // 128
+
+
 def test_workgroup_splits_keep_plans_allocation_free():
     """A long product of few tiles splits its contraction over workgroups; a
     plan whose tensors would fill the static scratch of allocation-free
