@@ -1187,7 +1187,9 @@ static std::string dma_loader(const KInfo& ki, const GemmSpec& sp, const std::ma
   s << "    const int q = (wb_ + i * " << R.gb << ") * 64 + l, k = q / " << P << ", p = q % " << P << ";\n";
   s << "    " << boffs << "[i] = (" << OT_ << ")((i64)k * " << sp.N << "LL + n0 + ((p ^ " << dma_fk(sp, "k") << ") * 8));\n  }\n";
   if (sp.dsb == 3) s << "  }\n";
-  const char* ld = "      asm volatile(\"s_mov_b32 m0, %1\\n\\tglobal_load_lds_dwordx4 %0, off\" :: \"v\"(src), \"s\"(la) : \"memory\", \"m0\");\n";
+  // (the wait state that gfx9 asks for between the write of M0 and the load is
+  // spelled out, since the compiler does not see into the statement)
+  const char* ld = "      asm volatile(\"s_mov_b32 m0, %1\\n\\ts_nop 0\\n\\tglobal_load_lds_dwordx4 %0, off\" :: \"v\"(src), \"s\"(la) : \"memory\", \"m0\");\n";
   s << "  auto dmaA_ = [&](const int kt, const int st) {\n#pragma unroll\n    for (int i = 0; i < " << R.PA << "; ++i) {\n";
   s << "      const " << T << "* src = Ag_ + (i64)kt * 64 + " << aoffs << "[i];\n";
   s << "      const unsigned la = lds0_ + (unsigned)((st * " << SAE << " + (wa_ + i * " << R.ga << ") * 512) * 2);\n" << ld;

@@ -1,4 +1,9 @@
-"""Shared test helpers: seeded inputs as float64 and the tolerance rule."""
+"""Shared test helpers: seeded inputs as float64, the tolerance rule and a
+check of the wait states of direct-to-LDS loads in compiled kernels."""
+
+import re
+import subprocess
+import tempfile
 
 import numpy as np
 
@@ -41,3 +46,53 @@ def close_elementwise(got, ref, rtol, atol):
     big = np.abs(ref) > atol / rtol
     rel = float(np.max(err[big] / np.abs(ref[big]))) if np.any(big) else 0.0
     return ok, (float(err.max()) if err.size else 0.0), rel
+
+
+OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
+
+
+def disassemble(code):
+    """Instructions of a gfx950 code object built here, as (opcode, [operands])."""
+    with tempfile.NamedTemporaryFile(suffix=".co") as f:
+        f.write(code)
+        f.flush()
+        text = subprocess.run([OBJDUMP, "-d", "--mcpu=gfx950", f.name], capture_output=True, text=True, check=True).stdout
+    out = []
+    for line in text.splitlines():
+        if line.startswith("\t"):
+            op, _, rest = line.split("//")[0].strip().partition(" ")
+            out.append((op, [t.strip() for t in rest.split(",") if t.strip()]))
+    return out
+
+
+def _sgprs(operand):
+    m = re.fullmatch(r"s(?:(\d+)|\[(\d+):(\d+)\])", operand)
+    return set() if not m else {int(m[1])} if m[1] else set(range(int(m[2]), int(m[3]) + 1))
+
+
+def lds_load_faults(ins):
+    """(number of direct-to-LDS loads, faults).  The loads are inline assembly,
+    whose hazards the compiler does not see.  On gfx9 a scalar write of M0 (the
+    load's LDS address) needs one wait state before the load, and a vector
+    instruction's write of a scalar register five before a memory instruction
+    that reads it (its buffer descriptor or scalar offset); nothing else may use
+    M0.  Distances are counted back in program order (an instruction is one wait
+    state, s_nop n is n + 1)."""
+    loads = [i for i, (op, a) in enumerate(ins) if op.startswith("global_load_lds") or (a and a[-1].split()[-1] == "lds")]
+    faults = []
+    for i, (op, a) in enumerate(ins):
+        if "m0" in a and not (op == "s_mov_b32" and a[0] == "m0" and ins[i + 1][0] == "s_nop" and i + 2 in loads):
+            faults.append(f"m0: {op} {a} then {ins[i + 1]}")
+    for i in loads:
+        if ins[i - 2][:1] + tuple(ins[i - 2][1][:1]) != ("s_mov_b32", "m0"):
+            faults.append(f"load without its own M0: {ins[i]}")
+        reads = set().union(*(_sgprs(t.split()[0]) for t in ins[i][1]))
+        states = 0
+        for op, a in reversed(ins[:i]):
+            if states >= 5:
+                break
+            dests = a[: 2 if "_co_" in op or "div_scale" in op else 1]
+            if op.startswith("v_") and any(_sgprs(t) & reads for t in dests):
+                faults.append(f"{op} {a} {states} wait states before {ins[i]}")
+            states += int(a[0], 0) + 1 if op == "s_nop" else 1
+    return len(loads), faults
