@@ -504,7 +504,7 @@ static std::string phased_mainloop(const GemmSpec& sp, int64_t KTG, bool exact) 
     }
     return o.str();
   };
-  if (sp.KSEQ > 1) s << "  f32x4 acc0_[" << sp.FM << "][" << sp.FN << "];  // kgrp 0: the sums of the first half of the k-tiles\n";
+  if (sp.KSEQ > 1) s << "  f32x4 acc0_[" << sp.FM << "][" << sp.FN << "];  // the sums of the first half of the k-tiles\n";
   s << "  const int nkt_ = kt1 - kt0;\n  (void)nkt_;\n";
   const int64_t KS = exact ? KTG : KTG - 1;  // k-tiles that every group has
   for (int t = 0; t < NST && t < KTG; ++t)

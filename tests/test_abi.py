@@ -378,36 +378,51 @@ def test_column_moments_kernel():
                              {ids[k] for k in ("mu", "D2", "var")}), [ids["out"]])])
 
 
+# What a product's main loop is, read off its code (comments aside).
+def _loop(src):
+    import re
+    code = re.sub(r"//[^\n]*", "", src)
+    return dict(phased="offen lds" in code, dma="global_load_lds" in code, registers="stashA" in code, kgroups="kgrp" in code,
+                wg_split="split_" in code, halves="acc0_" in code)
+
+
 def test_gemm_k_split_selection(monkeypatch):
-    """GEMM2 of the MLP block (256 tiles, 48 k-tiles) and of the odd-k test shape
-    use the intra-workgroup split of K; GEMM1 (256 x 192 tiles of eight waves)
-    and KORCH_GEMM_NO_KSPLIT=1 do not.  Asked for (KORCH_GEMM_DMA8=1), the split
-    gives way to eight waves over the whole contraction where both operands can
-    be staged three k-tiles deep (tiles of 128 rows dividing the problem), and
-    stays for ragged rows and for 64-row tiles."""
+    """The second product of the MLP block (256 tiles, 48 k-tiles) runs the phased
+    loop, whose one group of eight waves sums the contraction in two halves;
+    few tiles take its two k-groups (and, when long enough, a split over
+    workgroups).  KORCH_GEMM_PHASED=0 gives the register-staged
+    intra-workgroup split of K; the first product (256 x 192 tiles of eight
+    waves) has no split, nor has any with KORCH_GEMM_NO_KSPLIT=1.  Asked for
+    (KORCH_GEMM_DMA8=1), that split gives way to eight waves over the whole
+    contraction where both operands can be staged three k-tiles deep (tiles of
+    128 rows dividing the problem), and stays for ragged rows and for 64-row
+    tiles."""
     from paper_2406_09465_amd.warm import GEMM_CASES
 
-    def sources(sizes, flag):
-        monkeypatch.delenv("KORCH_GEMM_NO_KSPLIT", raising=False)
-        if flag:
-            monkeypatch.setenv("KORCH_GEMM_NO_KSPLIT", flag)
+    def products(sizes, **env):
+        for var in ("KORCH_GEMM_PHASED", "KORCH_GEMM_NO_KSPLIT", "KORCH_GEMM_DMA8"):
+            monkeypatch.delenv(var, raising=False)
+        for var, v in env.items():
+            monkeypatch.setenv(var, v)
         p = graphs.build("mlp", **sizes).plan("layered")
         p.compile()
-        return [p.kernel_source(k) for k in range(p.num_kernels())], [p.kernel_launch(k) for k in range(3)]
+        src = [p.kernel_source(k) for k in range(p.num_kernels())]
+        return [_loop(t) for t in src], [p.kernel_launch(k) for k in range(3)], src
 
-    monkeypatch.delenv("KORCH_GEMM_DMA8", raising=False)
-    for sz in [{}] + GEMM_CASES:
-        src, launch = sources(sz, "")
-        assert "kgrp" in src[2] and launch[2][1][0] == 512, sz
-        src, launch = sources(sz, "1")
-        assert "kgrp" not in src[2] and launch[2][1][0] == 256, sz
-    src, _ = sources({}, "")
-    assert "kgrp" not in src[1]
-    monkeypatch.setenv("KORCH_GEMM_DMA8", "1")
+    plain = dict(phased=False, dma=False, registers=False, kgroups=False, wg_split=False, halves=False)
+    for sz, form in zip([{}] + GEMM_CASES, [dict(halves=True), dict(kgroups=True), dict(kgroups=True, wg_split=True)]):
+        loop, launch, _ = products(sz)
+        assert loop[2] == {**plain, "phased": True, **form} and launch[2][1][0] == 512, sz
+        loop, launch, _ = products(sz, KORCH_GEMM_PHASED="0")
+        assert loop[2] == {**plain, "registers": True, "kgroups": True} and launch[2][1][0] == 512, sz
+        loop, launch, _ = products(sz, KORCH_GEMM_NO_KSPLIT="1")
+        assert not loop[2]["kgroups"] and not loop[2]["phased"] and launch[2][1][0] == 256, sz
+    loop, _, src = products({})
+    assert loop[1] == {**plain, "dma": True} and "kgrp" not in src[2]  # nor in a comment
     for sz, dma8 in zip([{}] + GEMM_CASES, [True, False, False]):
-        src, launch = sources(sz, "")
+        loop, launch, src = products(sz, KORCH_GEMM_DMA8="1")
         assert launch[2][1][0] == 512, sz
-        assert ("3 A stages and 3 B stages" in src[2]) == dma8 and ("kgrp" in src[2]) != dma8, sz
+        assert ("3 A stages and 3 B stages" in src[2]) == dma8 and loop[2] == {**plain, "dma": dma8, "registers": not dma8, "kgroups": not dma8}, sz
 
 
 def test_gemm_wide_tile_selection():
@@ -457,6 +472,7 @@ def test_gemm_direct_to_lds_staging_selection(monkeypatch):
     monkeypatch.delenv("KORCH_GEMM_DMA8", raising=False)
     monkeypatch.delenv("KORCH_GEMM_DMA_A3", raising=False)
     monkeypatch.delenv("KORCH_GEMM_DMA_STAGES", raising=False)
+    monkeypatch.delenv("KORCH_GEMM_PHASED", raising=False)
     (grid, block, lds), src = gemm1({})
     assert "32 A blocks and 24 B blocks of 1 KiB per k-tile, 2 A stages and 3 B stages" in src
     assert lds == (2 * 256 + 3 * 192) * 64 * 2
@@ -464,7 +480,7 @@ def test_gemm_direct_to_lds_staging_selection(monkeypatch):
     assert set(re.findall(r"s_waitcnt vmcnt\((\d+)\)", src)) == {"0"}
     assert "stashA" not in src
     _, src = gemm1(BIG_TILE_CASE)
-    assert "global_load_lds_dwordx4" not in src and "stashA" in src
+    assert _loop(src)["registers"] and not _loop(src)["dma"] and not _loop(src)["phased"]
     # asked for (KORCH_GEMM_DMA8=1), the second product (one 128 x 96 tile per
     # compute unit, K = 3072) runs eight waves of 32 x 48 over the whole
     # contraction with three stages of each operand (both loaded two k-tiles
@@ -479,16 +495,18 @@ def test_gemm_direct_to_lds_staging_selection(monkeypatch):
         (_, block2, lds2), src2 = p.kernel_launch(2), p.kernel_source(2)
         assert f"16 A blocks and 12 B blocks of 1 KiB per k-tile, {stages} A stages and {stages} B stages" in src2
         assert block2 == (512, 1, 1) and lds2 == stages * (128 + 96) * 64 * 2
-        assert "kgrp" not in src2 and par in src2
+        assert _loop(src2) == dict(phased=False, dma=True, registers=False, kgroups=False, wg_split=False, halves=False) and par in src2
         assert set(re.findall(r"s_waitcnt vmcnt\((\d+)\)", src2)) == {"0"}
     monkeypatch.delenv("KORCH_GEMM_DMA_STAGES")
     monkeypatch.delenv("KORCH_GEMM_DMA8")
-    # by default the split keeps register staging; asked for direct-to-LDS
-    # staging, each group of four waves has its own 68 KiB of stages (two
-    # groups, 136 KiB)
+    # the intra-workgroup split (without the phased loop) keeps register
+    # staging; asked for direct-to-LDS staging, each group of four waves has its
+    # own 68 KiB of stages (two groups, 136 KiB)
+    monkeypatch.setenv("KORCH_GEMM_PHASED", "0")
     p = graphs.build("mlp").plan("layered")
     p.compile()
-    assert "global_load_lds_dwordx4" not in p.kernel_source(2) and "kgrp" in p.kernel_source(2)
+    assert _loop(p.kernel_source(2)) == dict(phased=False, dma=False, registers=True, kgroups=True, wg_split=False, halves=False)
+    monkeypatch.delenv("KORCH_GEMM_PHASED")
     monkeypatch.setenv("KORCH_GEMM_DMA_KSPLIT", "1")
     p = graphs.build("mlp").plan("layered")
     p.compile()
@@ -502,7 +520,7 @@ def test_gemm_direct_to_lds_staging_selection(monkeypatch):
     assert "2 A stages and 2 B stages" in src and lds == (2 * 256 + 2 * 192) * 64 * 2
     monkeypatch.setenv("KORCH_GEMM_DMA", "0")
     _, src = gemm1({})
-    assert "global_load_lds_dwordx4" not in src and "stashA" in src
+    assert _loop(src)["registers"] and not _loop(src)["dma"] and not _loop(src)["phased"]
 
 
 @pytest.mark.parametrize("workload,plan,sizes", [

@@ -43,9 +43,11 @@ def _run(sizes, raw):
 
 
 def test_dma_staging_k_split_matches_register_staging(monkeypatch):
-    """The MLP block's second product (an intra-workgroup split of K) with
-    direct-to-LDS staging asked for (KORCH_GEMM_DMA_KSPLIT=1): oracle parity
-    and the same bytes as register staging."""
+    """The MLP block's second product as an intra-workgroup split of K with
+    direct-to-LDS staging asked for (KORCH_GEMM_DMA_KSPLIT=1): oracle parity,
+    the same bytes as that split with register staging (KORCH_GEMM_PHASED=0)
+    and as the phased loop that runs by default, which sums the contraction in
+    the same two halves."""
     print("\n[case] mlp layered, k-split product with direct-to-LDS staging", flush=True)
     raw, ref = reference("mlp", {})
     monkeypatch.delenv("KORCH_GEMM_DMA", raising=False)
@@ -56,10 +58,14 @@ def test_dma_staging_k_split_matches_register_staging(monkeypatch):
     ok, mx, rel = close(out["out"], ref["out"], TOL[w.dtype])
     assert ok, f"max abs err {mx:.3e}, normwise rel {rel:.3e}"
     monkeypatch.delenv("KORCH_GEMM_DMA_KSPLIT")
+    monkeypatch.setenv("KORCH_GEMM_PHASED", "0")
     _, r0, _, _, srcs0 = _run({}, raw)
-    assert "global_load_lds_dwordx4" not in srcs0[2]
-    for a, b in zip(r.outs, r0.outs):
-        assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+    assert "kgrp" in srcs0[2] and "stashA" in srcs0[2] and "lds_dwordx4" not in srcs0[2] and "offen lds" not in srcs0[2]
+    monkeypatch.delenv("KORCH_GEMM_PHASED")
+    _, r1, _, _, srcs1 = _run({}, raw)
+    assert "offen lds" in srcs1[2] and "kgrp" not in srcs1[2]
+    for a, b, c in zip(r.outs, r0.outs, r1.outs):
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16)) and torch.equal(a.view(torch.int16), c.view(torch.int16))
 
 
 @pytest.mark.parametrize("stages", ["", "2"])
@@ -78,7 +84,7 @@ def test_dma_staging_matches_register_staging(sizes, stages, monkeypatch):
     else:
         monkeypatch.delenv("KORCH_GEMM_DMA_2STAGE", raising=False)
     w, r, out, ndma, srcs = _run(sizes, raw)
-    assert ndma >= 1
+    assert ndma >= 1 and not any("offen lds" in s for s in srcs)
     want = "2 B stages" if stages else None
     if want:
         assert any(want in s for s in srcs)
@@ -86,8 +92,8 @@ def test_dma_staging_matches_register_staging(sizes, stages, monkeypatch):
     assert ok, f"mlp {sizes}: max abs err {mx:.3e}, normwise rel {rel:.3e}"
     monkeypatch.setenv("KORCH_GEMM_DMA", "0")
     monkeypatch.delenv("KORCH_GEMM_DMA_2STAGE", raising=False)
-    _, r0, _, ndma0, _ = _run(sizes, raw)
-    assert ndma0 == 0
+    _, r0, _, ndma0, srcs0 = _run(sizes, raw)
+    assert ndma0 == 0 and not any("offen lds" in s for s in srcs0)
     for a, b in zip(r.outs, r0.outs):
         assert a.dtype == b.dtype and torch.equal(a.view(torch.int16), b.view(torch.int16))
 
@@ -114,8 +120,8 @@ def test_eight_wave_dma_matches_register_staging(sizes, stages, monkeypatch):
     monkeypatch.setenv("KORCH_GEMM_NO_KSPLIT", "1")
     monkeypatch.delenv("KORCH_GEMM_DMA8")
     monkeypatch.delenv("KORCH_GEMM_DMA_STAGES")
-    _, r0, _, ndma0, _ = _run(sizes, raw)
-    assert ndma0 == 0
+    _, r0, _, ndma0, srcs0 = _run(sizes, raw)
+    assert ndma0 == 0 and not any("offen lds" in s for s in srcs0)
     for a, b in zip(r.outs, r0.outs):
         assert a.dtype == b.dtype and torch.equal(a.view(torch.int16), b.view(torch.int16))
 

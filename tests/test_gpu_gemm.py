@@ -3,9 +3,10 @@ float64 oracle.
 
 GEMM2 of an MLP block whose tiles leave one workgroup per compute unit and
 whose contraction is long runs as two groups of four waves over the two halves
-of the k-tiles; the shapes cover an odd number of k-tiles (the second group
-runs one tile fewer) with ragged rows, and an even number.  Each case also runs
-with the split switched off (KORCH_GEMM_NO_KSPLIT=1).
+of the k-tiles, in the phased loop and (KORCH_GEMM_PHASED=0) staged through
+registers; the shapes cover an odd number of k-tiles (the second group runs one
+tile fewer) with ragged rows, and an even number.  Each case also runs with the
+split switched off (KORCH_GEMM_NO_KSPLIT=1).
 """
 
 import pytest
@@ -24,20 +25,23 @@ def _gpu():
         pytest.skip("no GPU")
 
 
-@pytest.mark.parametrize("no_split", ["", "1"])
+@pytest.mark.parametrize("switch", ["", "KORCH_GEMM_PHASED=0", "KORCH_GEMM_NO_KSPLIT=1"])
 @pytest.mark.parametrize("plan", ["layered", "fused"])
 @pytest.mark.parametrize("sizes", GEMM_CASES, ids=lambda s: "x".join(str(v) for v in s.values()))
-def test_gemm_k_split(sizes, plan, no_split, monkeypatch):
+def test_gemm_k_split(sizes, plan, switch, monkeypatch):
     from paper_2406_09465_amd import graphs
     from paper_2406_09465_amd.runner import PlanRunner
-    monkeypatch.delenv("KORCH_GEMM_NO_KSPLIT", raising=False)
-    monkeypatch.delenv("KORCH_GEMM_DMA8", raising=False)
-    if no_split:
-        monkeypatch.setenv("KORCH_GEMM_NO_KSPLIT", no_split)
-    print(f"\n[case] mlp {sizes} {plan} no_split={no_split}", flush=True)
+    for var in ("KORCH_GEMM_NO_KSPLIT", "KORCH_GEMM_DMA8", "KORCH_GEMM_PHASED"):
+        monkeypatch.delenv(var, raising=False)
+    if switch:
+        monkeypatch.setenv(*switch.split("="))
+    print(f"\n[case] mlp {sizes} {plan} {switch}", flush=True)
     w = graphs.build("mlp", **sizes)
     raw, ref = reference("mlp", sizes)
-    out = PlanRunner(w, plan).run(raw)
+    r = PlanRunner(w, plan)
+    src = r.plan.kernel_source(r.plan.num_kernels() - 1)
+    assert ("offen lds" in src) == (not switch) and ("kgrp" in src) == ("NO_KSPLIT" not in switch)
+    out = r.run(raw)
     ok, mx, rel = close(out["out"], ref["out"], TOL[w.dtype])
     assert ok, f"mlp {sizes}: max abs err {mx:.3e}, normwise rel {rel:.3e}"
 
