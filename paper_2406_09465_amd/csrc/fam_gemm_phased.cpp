@@ -436,7 +436,10 @@ static std::string phased_mainloop(const GemmSpec& sp, int64_t KTG, bool exact) 
     for (int j = sp.FN * h / parts; j < sp.FN * (h + 1) / parts; ++j) o += readB(t, kk, j);
     return o;
   };
-  // waits until at most the loads of n tiles are in flight
+  // waits until at most the loads of n tiles are in flight: a wave's loads to
+  // LDS complete in issue order, also where some come from HBM, some from a
+  // cache and some lie out of the buffer's range (a probe of such mixes read
+  // 1.3e10 words after partial waits, all of them landed)
   auto wait = [&](int n) {
     auto w = [](int c) { return "asm volatile(\"s_waitcnt vmcnt(" + std::to_string(c) + ")\" ::: \"memory\");\n"; };
     if (!n || !PX) return "    " + w(n * PL);

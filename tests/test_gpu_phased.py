@@ -9,6 +9,8 @@ The bound per element is the output's rounding plus the fp32 accumulation of K
 products, K 2^-24 sum |a b| (each of the K additions rounds to 24 bits).
 """
 
+import ctypes as C
+
 import numpy as np
 import pytest
 
@@ -281,3 +283,62 @@ def test_phased_convolution(case):
     out = r.run(raw)
     ok, mx, rel = close(out["Y"], ref["Y"], TOL[dtype])
     assert ok, f"max abs err {mx:.3e}, normwise rel {rel:.3e}"
+
+
+# Waits on the oldest loads only, where loads take long and very differently:
+# every shape of three or more stages over a full chip, with a contraction that
+# ends inside a chunk (loads out of the buffer's range among the others), and
+# padded convolutions.  A tile read before it landed changes some bytes.
+def _repeat(r, what):
+    from paper_2406_09465_amd._abi import lib
+    r.launch_bound()
+    torch.cuda.synchronize()
+    first = [t.clone() for t in r.outs]
+    flush = torch.empty(512 << 20, dtype=torch.uint8, device="cuda")
+    stream = torch.cuda.current_stream().cuda_stream
+    for i in range(60):
+        for t in r.outs:
+            t.zero_()
+        if i >= 30:
+            assert lib.korch_flush_caches(C.c_void_p(flush.data_ptr()), C.c_size_t(flush.numel()), 0, C.c_void_p(stream)) == 0
+        r.launch_bound()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a.view(torch.uint8), b.view(torch.uint8)) for a, b in zip(first, r.outs)), f"{what}: execution {i}"
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("cfg", [c for c in SHAPES + F32_SHAPES if int(c.split(",")[6]) >= 3] + SPLITS + F32_SPLITS)
+def test_phased_repeats_bitwise(cfg, monkeypatch):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    monkeypatch.setenv("KORCH_GEMM_PHASED", cfg)
+    bm, bn, ks = int(cfg.split(",")[0]), int(cfg.split(",")[1]), int((cfg.split(",") + ["1"])[7])
+    dtype = "f32" if cfg in F32_SHAPES + F32_SPLITS else "bf16"
+    m, n, k = 16 * bm, (16 // ks if ks > 1 else 16) * bn, 1034 * ks + (1 if dtype == "f32" else 0)
+    print(f"\n[case] phased repeats {cfg} {m}x{n}x{k} {dtype}", flush=True)
+    r, x = _run(m, n, k, dtype, "residual", seed=k)
+    assert "offen lds" in r.plan.kernel_source(0)
+    rows = slice(0, m, 61)
+    full, r.outs = r.outs, [r.outs[0][rows]]
+    _check(r, {nm: v[rows] if nm in ("A", "R") else v for nm, v in x.items()}, k, dtype)
+    r.outs = full
+    _repeat(r, cfg)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", [("f16", 104, 104, 128, 256, 3), ("f32", 96, 90, 64, 128, 3)], ids=lambda c: "x".join(map(str, c)))
+def test_phased_convolution_repeats_bitwise(case):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2406_09465_amd import graphs
+    from paper_2406_09465_amd.runner import PlanRunner
+    from tests.helpers import inputs_f64
+    dtype, hh, ww, cin, cout, k = case
+    print(f"\n[case] phased conv repeats {case}", flush=True)
+    sizes = dict(hh=hh, ww=ww, cin=cin, cout=cout, k=k)
+    raw, _ = inputs_f64("conv", dtype=dtype, **sizes)
+    r = PlanRunner(graphs.build("conv", dtype=dtype, **sizes), "fused")
+    assert "offen lds" in r.plan.kernel_source(0)
+    r.set_inputs(raw)
+    r.bind()
+    _repeat(r, str(case))
