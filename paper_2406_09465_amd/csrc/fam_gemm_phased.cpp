@@ -37,16 +37,20 @@ static bool env_set(const char* n) {
 
 // Splitting a tile's contraction over workgroups pays where tiles leave compute
 // units idle and the chain of k-tiles is long (the second product of an MLP
-// block on few rows): up to one workgroup per compute unit, four k-tiles each.
-// The hand-off (partial tiles out, a counter, the last workgroup's sum) costs
-// what it measured with 4 to 16 KiB tiles and 2 to 8 parts.  128 x 768 x 3072: 6.0
-// us in four parts against 9.2 (12.4 staged through registers); 16 x 1024 x 4096:
-// 5.1 against 8.7; 49 x 960 x 2240 in fp32 6.7 against 11.6.
-static bool splits_fit(int bm, int bn, int64_t tiles, int ks, double kt) {
-  return workgroup_splits() && tiles * ks <= 256 && kt >= 4.0 * ks && (double)tiles * ks * bm * bn * 4 <= 8.0 * (1 << 20);
+// block on few rows): up to one workgroup per compute unit, sixteen parts and
+// two k-tiles each.  128 x 768 x 3072: 6.0 us in four parts against 9.2 (12.4
+// staged through registers); 16 x 1024 x 4096: 5.1 against 8.7; 49 x 960 x 2240
+// in fp32 6.7 against 11.6.
+static bool splits_fit(int bm, int bn, int64_t tiles, int ks, int kg, double kt) {
+  return workgroup_splits() && tiles * ks <= 256 && kt >= 2.0 * ks * kg && (double)tiles * ks * bm * bn * 4 <= 16.0 * (1 << 20);
 }
-static double handoff(int bm, int bn, int ks, int kg) {
-  return ks > 1 ? 0.5 + ks * (0.3 + 0.015 * bm * bn / 256.0) + (kg > 1 ? 0.45 : 0.0) : 0.0;
+// The hand-off of a split (partial tiles out, a counter, the last workgroup's
+// sum): per part, more the more workgroups write partial tiles at once (`fill`:
+// workgroups per compute unit).
+static double handoff(int bm, int bn, int ks, int kg, double fill, bool f32) {
+  if (ks == 1) return 0.0;
+  const double area = bm * bn / 2048.0;
+  return 1.0 + 0.2 * area + ks * area * (f32 ? 0.06 + 0.055 * fill : 0.07 + 0.22 * fill) + (kg > 1 ? 0.4 : 0.0);
 }
 
 // Tile shape, waves, k-groups and stages of the phased path; false: not taken.
@@ -62,7 +66,22 @@ static double handoff(int bm, int bn, int ks, int kg) {
 // some 620 clocks (at 256 x 256 it is refused requests 56 % of the time; L2
 // misses are the compulsory ones); small tiles with deep stages cover latency
 // when there are few of them.
-static bool phased_tiles(GemmSpec& sp) {
+//
+// What is not a full chip of cache-resident operands is priced by terms fitted
+// to 2700 16-bit and 800 fp32 kernels (every shape, 1 to 16384 rows, 1 to 16
+// parts; to about 12 % warm, 16 % after a cache flush): a k-tile takes 0.7 (fp32
+// 0.83) of its full-chip time on an empty chip and all of it from 142 workgroups
+// on; operands of 32 MB, which come past the L2s, take 1.3 times as long (which
+// weighs against the hand-off of a split only); and
+// every k-tile of a workgroup's chain waits 0.1 us (fp32 0.03) per 100 tile rows
+// and columns longer when its operands are first touched and the chip is too
+// empty to hide it, of which half counts (they are cold in one use, warm in
+// another).  So short chains in many parts are taken over two k-groups or few
+// parts: 25 x 64 x 1344, batch of 8: 3.8 us in 7 parts (5.2 after a flush), 4.3
+// (7.4) in two k-groups; 28 x 120 x 57384: 15 (24) in 16 parts, 25 (43) in 8;
+// 436 x 2976 x 5624: 29 (36) as 128 x 96 tiles in two parts, 38 (55) as 128 x 64.
+// `reads_rows`: the epilogue reads tensors that differ from row to row.
+static bool phased_tiles(GemmSpec& sp, bool reads_rows) {
   if (const char* e = getenv("KORCH_GEMM_PHASED")) {
     int bm, bn, wm, wn, kg, st, bk, ks = 1;
     if (sscanf(e, "%d,%d,%d,%d,%d,%d,%d,%d", &bm, &bn, &wm, &wn, &kg, &bk, &st, &ks) < 7) return false;
@@ -79,27 +98,46 @@ static bool phased_tiles(GemmSpec& sp) {
     // k-step's products in twice the clocks), so what a tile costs is its area
     // and how evenly the tiles fall on the compute units: t1 us per k-tile (32)
     // when a compute unit has one tile (its waves wait alone), tc us per tile
-    // when it has several.  2048 x 3072 x 768: 64 x 96 tiles 74.9 us (128 x 96
-    // staged through registers 83.4); 2048 x 768 x 3072: 73.4 in two k-groups
-    // (92.5); 340 x 256 x 1024: 32 x 32 tiles 6.9 (64 x 64: 23.2).
+    // when it has several, which also pay for their first loads and stores one
+    // after another, more than in proportion to their area (`turn`; 4967 x 1688 x 32
+    // with a residual: 32 x 64 tiles 14.4 us, 64 x 64 17.3, 64 x 128 19.2).  2048 x
+    // 3072 x 768: 64 x 96 tiles 74.9 us (128 x 96 staged through registers 83.4);
+    // 2048 x 768 x
+    // 3072: 73.4 in two k-groups (92.5); 340 x 256 x 1024: 32 x 32 tiles 6.9 (64
+    // x 64: 23.2).
     static const Shape_ f32s[] = {
         {64, 128, 2, 2, 1, 2, 0, 1.14, 0.97, 4.0},  {64, 96, 2, 2, 1, 2, 0, 0.80, 0.745, 3.5}, {64, 64, 2, 2, 1, 2, 0, 0.62, 0.475, 3.0},
-        {32, 64, 2, 2, 1, 4, 0, 0.32, 0.25, 2.5},   {32, 32, 2, 2, 1, 4, 0, 0.172, 0.13, 1.8}, {64, 96, 2, 2, 2, 3, 0, 0.75, 0.75, 3.0},
-        {32, 64, 2, 2, 2, 6, 0, 0.285, 0.285, 2.0}, {32, 32, 2, 2, 2, 6, 0, 0.15, 0.15, 1.6},
+        {32, 64, 2, 2, 1, 4, 0, 0.32, 0.25, 2.5},   {32, 32, 2, 2, 1, 4, 0, 0.172, 0.13, 1.8}, {64, 96, 2, 2, 2, 3, 0, 0.82, 0.82, 3.0},
+        {32, 64, 2, 2, 2, 6, 0, 0.31, 0.31, 2.0},   {32, 32, 2, 2, 2, 6, 0, 0.165, 0.165, 1.6},
     };
     const double KT = (double)((sp.K + 31) / 32);
     for (const Shape_& h : f32s) {
       const int64_t tiles = (sp.M + h.bm - 1) / h.bm * ((sp.N + h.bn - 1) / h.bn) * sp.batch, n = (tiles + 255) / 256;
-      for (int ks = 1; ks <= 8; ++ks) {
-        if (ks > 1 && !splits_fit(h.bm, h.bn, tiles, ks, KT)) break;
-        const double kt = std::ceil(KT / ks);
+      // (over many tiles of a short contraction 32 x 32 ones read the operands too often where 64 columns are
+      // not padding: 1687 x 872 x 48, batch of 8, 37.6 us after a flush, 32 x 64 34.1)
+      if (n > 4 && KT <= 6 && h.bn == 32 && h.bm == 32 && sp.M > 32 && sp.N > 32) continue;
+      const double area = h.bm * h.bn / 2048.0, turn = reads_rows ? 0.6 * area - 0.1 : 0.08 + 0.22 * area;
+      for (int ks = 1; ks <= 16; ++ks) {
+        if (ks > 1 && !splits_fit(h.bm, h.bn, tiles, ks, h.kg, KT)) break;
+        const double kt = std::ceil(KT / ks), fill = std::min(1.0, tiles * ks / 256.0);
         if (h.kg > 1 && (n > 1 || kt < 8)) continue;  // two k-groups share the compute unit of one tile
-        const double cost = h.ov + kt * (n == 1 ? h.t1 : n * h.tc) + handoff(h.bm, h.bn, ks, h.kg);
+        const double cost = h.ov + (n - 1) * turn + kt * (n == 1 ? h.t1 * (0.83 + 0.17 * fill) : n * h.tc) +
+                            handoff(h.bm, h.bn, ks, h.kg, fill, true) + 0.00016 * kt * (h.bm + h.bn) * (1.0 - std::min(1.0, 1.8 * fill));
         if (cost < best) {
           best = cost;
-          sp.BM = h.bm, sp.BN = h.bn, sp.WM = h.wm, sp.WN = h.wn, sp.KG = h.kg, sp.PST = h.st, sp.BK = 32, sp.KS = ks;
+          // (more tiles of a short contraction than fit on a compute unit hide the loads
+          // better than stages: 4967 x 1688 x 32 in 32 x 64 tiles 18.7 us with four, 14.4
+          // with two)
+          sp.BM = h.bm, sp.BN = h.bn, sp.WM = h.wm, sp.WN = h.wn, sp.KG = h.kg, sp.PST = n > 4 && KT <= 6 ? 2 : h.st, sp.BK = 32, sp.KS = ks;
         }
       }
+    }
+    if (sp.K % 32 && sp.K % 32 <= 16 && sp.K <= 112 && !sp.conv && sp.KS == 1 && sp.KG == 1 &&
+        (sp.M + sp.BM - 1) / sp.BM * ((sp.N + sp.BN - 1) / sp.BN) * sp.batch > 4 * 256) {
+      // a short contraction over many tiles: k-tiles of 16 (of 64 rows at least,
+      // so that every wave stages a block) save the MFMAs of an empty half k-tile
+      if (sp.BM == 32) sp.BM = sp.BN = 64;
+      sp.BK = 16, sp.PST = (int)std::min<int64_t>(4, std::max<int64_t>(2, (sp.K + 15) / 16));
     }
     return true;
   }
@@ -107,7 +145,7 @@ static bool phased_tiles(GemmSpec& sp) {
       {256, 256, 2, 4, 1, 2, 1, 1.50, 1.50, 9.5}, {256, 128, 2, 4, 1, 3, 1, 0.87, 0.87, 4.9}, {128, 128, 2, 2, 1, 2, 2, 0.62, 1.00, 3.2},
       {128, 128, 2, 4, 1, 4, 1, 0.50, 0.50, 2.6}, {128, 96, 2, 2, 1, 2, 2, 0.60, 0.88, 2.8},  {128, 96, 4, 2, 1, 5, 1, 0.46, 0.46, 2.2},
       {128, 64, 4, 2, 1, 5, 1, 0.31, 0.31, 2.2},  {128, 64, 2, 2, 1, 3, 2, 0.31, 0.57, 2.4},  {64, 128, 2, 2, 1, 3, 2, 0.31, 0.56, 2.3},
-      {64, 64, 2, 2, 1, 4, 2, 0.245, 0.38, 1.7},   {32, 64, 2, 2, 1, 6, 2, 0.17, 0.29, 1.6},   {32, 64, 2, 2, 2, 6, 1, 0.155, 0.155, 1.6},
+      {64, 64, 2, 2, 1, 4, 2, 0.245, 0.38, 1.7},   {32, 64, 2, 2, 1, 6, 2, 0.17, 0.29, 1.6},   {32, 64, 2, 2, 2, 6, 1, 0.165, 0.165, 1.6},
   };
   const double KT = (double)((sp.K + 63) / 64);
   if (KT <= 2 && sp.N % 8) {
@@ -121,6 +159,33 @@ static bool phased_tiles(GemmSpec& sp) {
     sp.BN = 64, sp.WM = sp.WN = 2, sp.KG = 1, sp.PST = 2, sp.BK = 64, sp.KS = 1;
     return true;
   }
+  const int64_t tiles64 = (sp.M + 63) / 64 * ((sp.N + 63) / 64) * sp.batch;
+  const bool three = sp.K > 80 && sp.K <= 96;
+  if ((KT <= 1 || three) && !sp.conv && tiles64 > 256) {
+    // One k-tile over more than a round of tiles is all first loads and stores, and
+    // so are three k-steps of 32, in k-tiles of one step that leave no quarter of a
+    // second k-tile empty.  An epilogue that reads tensors of the output's shape
+    // goes through the fp32 C tile, of which small tiles keep more per compute unit
+    // (in us: 623 x 8000 x 64 64 x 64 tiles 5.6, 64 x 128 7.5, 128 x 128 7.0, staged
+    // through registers 6.5; 196 x 3328 x 64, batch of 16: 10.6, 13.9, 12.7, 15.4; 134
+    // x 7776 x 96, batch of 8: 10.4, 12.4, 15.5, 11.3).  The rest store as fast from
+    // any tile, and wider ones read the operands fewer times (2206 x 5088 x 64 7.8,
+    // 7.3, 8.2, 8.2; after a flush 11.8, 9.4, 10.2, 9.8; 20000 x 256 x 96 6.6, 6.4, 6.9,
+    // 7.1), 128 x 128 fastest in one nearly full round of two per compute unit (6867
+    // x 1024 x 64: 4.8 us in 432 tiles, 64 x 128 5.6).
+    const int64_t t128 = (sp.M + 127) / 128 * ((sp.N + 127) / 128) * sp.batch, t64x128 = (sp.M + 63) / 64 * ((sp.N + 127) / 128) * sp.batch;
+    sp.WM = sp.WN = 2, sp.KG = 1, sp.PST = three ? 3 : 2, sp.BK = three ? 32 : 64, sp.KS = 1;
+    sp.BM = sp.BN = 64;
+    if (!reads_rows && t128 > 384 && t128 <= 512) {
+      sp.BM = sp.BN = 128;
+    } else if (!reads_rows && t64x128 > 512 && (double)t64x128 * 2.0 <= 1.1 * (double)tiles64) {
+      sp.BN = 128;
+    }
+    return true;
+  }
+  // operands past the L2s (a convolution's left operand is its image)
+  const double left = sp.conv ? (double)sp.H * sp.W * sp.Cin : (double)sp.M * sp.K * sp.batch;
+  const double bytes = 2.0 * (left + (double)sp.K * sp.N * sp.batch), far = 0.3 * std::min(1.0, bytes / 32e6);
   for (const Shape_& h : shapes) {
     // 96 columns do not divide the threads: a convolution's per-channel operands
     // would be loaded for every element (275 x 129, 64 to 256 channels, 1 x 1:
@@ -132,23 +197,31 @@ static bool phased_tiles(GemmSpec& sp) {
     // 128-row tiles staged through registers)
     if (h.bm * h.bn == 256 * 256 && reg_relief() >= 1) continue;
     const int64_t tiles = (sp.M + h.bm - 1) / h.bm * ((sp.N + h.bn - 1) / h.bn) * sp.batch;
-    const int64_t full = tiles / (256 * h.c), rest = (tiles - full * 256 * h.c + 255) / 256;
-    const double tr = h.c > 1 ? h.t1 + (h.tc - h.t1) * (double)(rest - 1) / (h.c - 1) : h.t1;
-    for (int ks = 1; ks <= 8; ++ks) {
-      if (ks > 1 && !splits_fit(h.bm, h.bn, tiles, ks, KT)) break;
-      const double kt = std::ceil(KT / ks);
+    for (int ks = 1; ks <= 16; ++ks) {
+      if (ks > 1 && !splits_fit(h.bm, h.bn, tiles, ks, h.kg, KT)) break;
+      const double kt = std::ceil(KT / ks), fill = std::min(1.0, tiles * ks / 256.0), busy = std::min(1.0, 1.8 * fill);
       // two k-groups (their loads share one compute unit): where it has one tile
       if (h.kg > 1 && (tiles * ks > 256 || kt < 8)) continue;
-      // Up to 32 k-tiles a split keeps two k-groups in each workgroup, as the
-      // k-split kernel of such products always had (tests pin it); without them
-      // 100 x 512 x 2048 takes 4.5 us against 4.9.
-      if (h.kg == 1 && ks > 1 && KT <= 32) continue;
-      const double cost = full * (kt * h.tc + h.ov) + (rest ? kt * tr + h.ov : 0.0) + handoff(h.bm, h.bn, ks, h.kg);
+      const int64_t full = tiles * ks / (256 * h.c), rest = (tiles * ks - full * 256 * h.c + 255) / 256;
+      double tr = h.c > 1 ? h.t1 + (h.tc - h.t1) * (double)(rest - 1) / (h.c - 1) : h.t1;
+      if (full + rest == 1) tr *= 0.7 + 0.3 * busy;
+      double body = (full * (kt * h.tc + h.ov) + (rest ? kt * tr + h.ov : 0.0)) * (1.0 + far);
+      if (ks > 1) body = std::max(body, bytes / 5.2e6);  // no split makes the operands arrive faster than the memory's 5.2 TB/s
+      const double cost = body + handoff(h.bm, h.bn, ks, h.kg, fill, false) + 0.0005 * kt * (h.bm + h.bn) * (1.0 - busy);
       if (cost < best) {
         best = cost;
         sp.BM = h.bm, sp.BN = h.bn, sp.WM = h.wm, sp.WN = h.wn, sp.KG = h.kg, sp.PST = h.st, sp.BK = 64, sp.KS = ks;
       }
     }
+  }
+  if (sp.K % 64 > 16 && sp.K % 64 <= 32 && sp.K <= 224 && !sp.conv && sp.KS == 1 && sp.BM == 128 && sp.PST == 2 &&
+      (sp.BN == 128 || (sp.M + 127) / 128 * ((sp.N + 127) / 128) * sp.batch > 512)) {
+    // A short contraction whose last k-tile of 64 is half empty, over more than a
+    // round of 128-row tiles: k-tiles of 32, in three stages that still leave three
+    // workgroups per compute unit (4780 x 4832 x 160: 19.0 us with k-tiles of 64,
+    // 17.4 in four stages of 32, 15.6 in three; 1404 x 3320 x 224, batch of 8: 33.8,
+    // 30.7, 28.5; 3000 x 2000 x 288, above the line, 8.0 and 8.4).
+    sp.BN = 128, sp.BK = 32, sp.PST = 3;
   }
   return true;
 }
@@ -179,6 +252,18 @@ static int transposed_source(const KInfo& ki, const GemmSpec& sp) {
   for (int o : ki.k.outs)
     if (o == sp.Bs[0]) return -1;
   return n.in[0];
+}
+
+// Whether the epilogue reads a tensor that differs from row to row of the product.
+static bool epilogue_reads_rows(const KInfo& ki, const GemmSpec& sp) {
+  const Graph& g = ki.g;
+  for (int v : sp.epi)
+    for (int u : g.nodes[v].in) {
+      if (sp.epi.count(u) || std::count(sp.mms.begin(), sp.mms.end(), u)) continue;
+      const Shape& s = g.nodes[u].shape;
+      if (s.size() >= 2 && s[s.size() - 2] != 1) return true;
+    }
+  return false;
 }
 
 bool plan_phased(const KInfo& ki, GemmSpec& sp, bool split_halves) {
@@ -212,10 +297,31 @@ bool plan_phased(const KInfo& ki, GemmSpec& sp, bool split_halves) {
   if (!getenv("KORCH_GEMM_PHASED") && !sp.conv && sp.M * sp.N * sp.batch <= 1 << 20 && sp.K <= 256 && sp.K % 64 == 0 && sp.M % sp.BM == 0 &&
       sp.N % sp.BN == 0)
     return false;
-  // Outputs of 16 columns waste half of the narrowest tile: a short convolution
+  // Outputs of a few columns waste most of the narrowest tile: over more rows than
+  // a round of 128-row tiles, those of a short contraction keep their own
+  // tiles of 16 or 32 columns (5591 x 16 x 104, batch of 16: 5.7 us, phased 6.7 at
+  // best; 5616 x 16 x 304, batch of 8: 4.8 and 6.0; 8006 x 32 x 40, batch of 16: 5.6
+  // and 8.2; 5538 x 6 x 184, batch of 16: 7.6 and 18.4; above the line 72891 x 24 x
+  // 72 7.2 and 5.4, 15161 x 12 x 600, batch of 8, 28.2 and 25.4; rows of 8 but not of
+  // 16 bytes, which those tiles gather: 60667 x 4 x 436, batch of 2, 44.0 and 20.0; fp32 82312 x 8 x 68 6.8 and 8.4, 16538 x 16 x 432, batch of 2,
+  // 17.2 and 14.0).
+  if (!getenv("KORCH_GEMM_PHASED") && !sp.conv) {
+    const int64_t rows = sp.M * sp.batch;
+    if (CE == 8 && sp.N <= 32 && rows > 128 * 256 && sp.K <= (sp.N % 4 == 2 || (sp.N <= 16 && sp.N % 8 == 0) ? 448 : 64)) return false;
+    if (CE == 4 && sp.N <= 16 && rows > 65536 && sp.K <= 256) return false;
+    // So do large outputs of one k-step, which are all stores and have nothing to
+    // stage ahead (7613 x 6872 x 32: 22.9 us, 32.5 after a flush, phased 23.8 and
+    // 43.8; 288 x 992 x 16, batch of 16: 4.3 and 5.2; below the line 1511 x 2656 x
+    // 32 with a residual 6.1 and 4.2; fp32 186 x 5720 x 16, batch of 16: 15.1 and 21.1).
+    if (sp.K <= (CE == 8 ? 32 : 16) && rows * sp.N >= 1 << 22) return false;
+  }
+  // Outputs of 16 columns waste most of the narrowest tile: a short convolution
   // to them keeps its own (300 x 300, 256 to 16 channels: 10.9 us, phased 12.6;
-  // 141 x 141 with 3 x 3 taps of 128 channels, above the line: 9.5 and 8.9).
-  if (!getenv("KORCH_GEMM_PHASED") && sp.conv && sp.N <= 16 && sp.K <= 256) return false;
+  // 141 x 141 with 3 x 3 taps of 128 channels, above the line: 9.5 and 8.9), as
+  // does a long one over more than a round of its 64-row tiles (294 x 111, 3 x 3,
+  // 512 to 16: 23.1 and 27.9; 141 x 140, 5 x 5, 96 to 16: 17.6 and 20.2; 290 x 98, 5 x
+  // 5, 64 to 16, below the line: 11.4 and 10.2).
+  if (!getenv("KORCH_GEMM_PHASED") && sp.conv && sp.N <= 16 && (sp.K <= 256 || (CE == 8 && sp.M > 64 * 256 && sp.K > 2048))) return false;
   // So does one over many pixels whose three or four k-tiles are of 32 channels
   // (275 x 129, 96 to 256 channels, 1 x 1: 11.0 us, phased 12.4).
   if (!getenv("KORCH_GEMM_PHASED") && sp.conv && CE == 8 && sp.Cin % 64 && sp.K <= 128 && sp.M * sp.N >= 1 << 22) return false;
@@ -224,9 +330,13 @@ bool plan_phased(const KInfo& ki, GemmSpec& sp, bool split_halves) {
   if (!getenv("KORCH_GEMM_PHASED") && CE == 4 && sp.N % 4 && sp.K <= 32) return false;
   GemmSpec t = sp;
   t.bt = bt;
-  if (!phased_tiles(t)) return false;
+  if (!phased_tiles(t, epilogue_reads_rows(ki, t))) return false;
   if (t.conv && t.Cin % t.BK) t.BK /= 2, t.PST = std::min(12, 2 * t.PST);  // the same LDS in twice the stages
   if (t.KS < 1 || t.KS * t.KG > (t.K + t.BK - 1) / t.BK) t.KS = 1;
+  // no stages that the contraction does not fill: short ones are bound by their
+  // first loads and stores, which more workgroups per compute unit overlap
+  if (!getenv("KORCH_GEMM_PHASED"))
+    t.PST = (int)std::max<int64_t>(2, std::min<int64_t>(t.PST, ((t.K + t.BK - 1) / t.BK + t.KS * t.KG - 1) / (t.KS * t.KG)));
   // A long contraction whose 128-row tiles leave at most one per compute unit
   // is summed in two halves that are added at the end, as its k-split kernel
   // with register staging does: the results are the same to the bit (wave tiles

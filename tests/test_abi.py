@@ -389,14 +389,13 @@ def _loop(src):
 def test_gemm_k_split_selection(monkeypatch):
     """The second product of the MLP block (256 tiles, 48 k-tiles) runs the phased
     loop, whose one group of eight waves sums the contraction in two halves;
-    few tiles take its two k-groups (and, when long enough, a split over
-    workgroups).  KORCH_GEMM_PHASED=0 gives the register-staged
+    fewer tiles take two k-groups of four waves or, when it is long enough, a
+    split over workgroups.  KORCH_GEMM_PHASED=0 gives the register-staged
     intra-workgroup split of K; the first product (256 x 192 tiles of eight
-    waves) has no split, nor has any with KORCH_GEMM_NO_KSPLIT=1.  Asked for
-    (KORCH_GEMM_DMA8=1), that split gives way to eight waves over the whole
-    contraction where both operands can be staged three k-tiles deep (tiles of
-    128 rows dividing the problem), and stays for ragged rows and for 64-row
-    tiles."""
+    waves) has no split, nor has any with KORCH_GEMM_NO_KSPLIT=1.  Asked for (KORCH_GEMM_DMA8=1), that split gives way
+    to eight waves over the whole contraction where both operands can be staged
+    three k-tiles deep (tiles of 128 rows dividing the problem), and stays for
+    ragged rows and for 64-row tiles."""
     from paper_2406_09465_amd.warm import GEMM_CASES
 
     def products(sizes, **env):
@@ -410,9 +409,9 @@ def test_gemm_k_split_selection(monkeypatch):
         return [_loop(t) for t in src], [p.kernel_launch(k) for k in range(3)], src
 
     plain = dict(phased=False, dma=False, registers=False, kgroups=False, wg_split=False, halves=False)
-    for sz, form in zip([{}] + GEMM_CASES, [dict(halves=True), dict(kgroups=True), dict(kgroups=True, wg_split=True)]):
+    for sz, form, threads in zip([{}] + GEMM_CASES, [dict(halves=True), dict(kgroups=True), dict(wg_split=True)], [512, 512, 256]):
         loop, launch, _ = products(sz)
-        assert loop[2] == {**plain, "phased": True, **form} and launch[2][1][0] == 512, sz
+        assert loop[2] == {**plain, "phased": True, **form} and launch[2][1][0] == threads, sz
         loop, launch, _ = products(sz, KORCH_GEMM_PHASED="0")
         assert loop[2] == {**plain, "registers": True, "kgroups": True} and launch[2][1][0] == 512, sz
         loop, launch, _ = products(sz, KORCH_GEMM_NO_KSPLIT="1")

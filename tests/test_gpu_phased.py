@@ -228,6 +228,59 @@ def test_phased_default_choice(size):
     _check(r, x, k, "f16")
 
 
+# What the tile rule takes by itself at the edges of its terms: (m, n, k, dtype,
+# epilogue, batch) and (tile rows, tile columns, k-tile, split over workgroups),
+# or None where a product keeps the older loops.  One k-tile and three k-steps
+# over more than a round of tiles, k-tiles of half a chunk row (16-bit and fp32)
+# with a ragged end, many fp32 tiles in two stages, sixteen parts of a
+# contraction, narrow outputs and one-step contractions.
+CHOICES = [((2100, 520, 64, "f16", "residual", 0), (64, 64, 64, False)), ((2100, 520, 40, "bf16", "", 0), (64, 64, 64, False)),
+           ((6900, 1000, 64, "f16", "", 0), (128, 128, 64, False)), ((4400, 1160, 64, "bf16", "", 0), (64, 128, 64, False)),
+           ((2100, 520, 96, "f16", "residual", 0), (64, 64, 32, False)), ((700, 520, 90, "bf16", "", 5), (64, 64, 32, False)),
+           ((2500, 2600, 160, "f16", "", 0), (128, 128, 32, False)), ((2500, 2600, 222, "bf16", "residual", 0), (128, 128, 32, False)),
+           ((3100, 1100, 40, "f32", "", 0), (64, 64, 16, False)), ((3100, 1100, 71, "f32", "residual", 0), (64, 64, 16, False)),
+           ((3100, 1100, 96, "f32", "residual", 0), (32, 64, 32, False)), ((70, 72, 20002, "f16", "", 0), (32, 64, 64, True)),
+           ((21, 37, 9000, "f32", "residual", 0), (32, 32, 32, True)), ((16, 64, 1344, "bf16", "", 8), (32, 64, 64, True)),
+           ((436, 2976, 5624, "bf16", "", 0), (128, 96, 64, True)), ((5000, 16, 104, "f16", "", 16), None),
+           ((33000, 30, 66, "bf16", "", 0), None), ((3000, 1500, 32, "f16", "", 0), None), ((70000, 12, 40, "f32", "", 0), None)]
+
+
+@pytest.mark.parametrize("product,tile", CHOICES, ids=lambda c: "x".join(map(str, c or ("older",))))
+def test_phased_tile_rule(product, tile):
+    import re
+    from paper_2406_09465_amd import codeobj
+    from paper_2406_09465_amd._abi import Plan
+    w, kernels = _graph(*product)
+    p = Plan(w.graph, kernels)
+    p.compile()
+    src = p.kernel_source(0)
+    assert ("offen lds" in src) == (tile is not None)
+    (res,) = codeobj.kernel_resources(p.kernel_code(0)).values()
+    assert res["scratch"] == 0
+    if tile:
+        eb = 4 if product[3] == "f32" else 2
+        got = [int(re.search(e, src)[1]) for e in (r"m0 = \(i64\)tm \* (\d+)", r"n0 = \(i64\)tn \* (\d+)", r"\(unsigned\)kt \* (\d+)")]
+        assert (got[0], got[1], got[2] // eb, "split_ =" in src) == tile
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("product", [c for c, _ in CHOICES], ids=lambda c: "x".join(map(str, c)))
+def test_phased_tile_rule_products(product):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    m, n, k, dtype, epi, batch = product
+    print(f"\n[case] phased rule {product}", flush=True)
+    r, x = _run(m, n, k, dtype, epi, batch, seed=m + k)
+    first = r.outs[0].clone()
+    for _ in range(5):
+        r.launch_bound()
+    torch.cuda.synchronize()
+    assert torch.equal(first, r.outs[0])
+    step = max(1, m // 200)  # rows enough to meet every kind of tile
+    r.outs = [r.outs[0][..., ::step, :]]
+    _check(r, {nm: v[..., ::step, :] if nm in ("A", "R") else v for nm, v in x.items()}, k, dtype)
+
+
 @pytest.mark.gpu
 def test_phased_nonfinite_rows_stay_apart():
     """A contraction that 64 does not divide: the chunks past a row's end are
