@@ -252,10 +252,12 @@ int korch_plan_execute(korch_plan* p, const void* const* inputs, void* const* ou
    process ends; korch_plan_load looks up its address on each device.  The
    call first clears the counters the plan uses with a fill kernel on
    `stream`, then launches the plan's kernels; it never allocates, compiles,
-   loads or synchronizes.  Errors: KORCH_E_STATE when the plan is not loaded
-   on the current device; KORCH_E_WORKSPACE when the plan's workspace
-   (korch_plan_workspace_bytes) or counters exceed the static array (nothing
-   is launched); KORCH_E_ARG / KORCH_E_ALIGN as korch_plan_execute.  Every
+   loads or synchronizes.  A plan whose workspace (korch_plan_workspace_bytes)
+   fits the static array only without the partial sums of contractions split
+   over workgroups runs kernels without such splits here (the same sums in
+   another order).  Errors: KORCH_E_STATE when the plan is not loaded on the
+   current device; KORCH_E_WORKSPACE when workspace or counters exceed the
+   static array either way (nothing is launched); KORCH_E_ARG / KORCH_E_ALIGN as korch_plan_execute.  Every
    call on one device shares that device's array and finds there whatever the
    previous call left: calls that overlap on one device (two streams, or two
    threads without ordering) race and give wrong results. */

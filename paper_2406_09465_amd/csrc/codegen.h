@@ -84,8 +84,8 @@ void set_reg_relief(int level);
 int reg_relief();
 constexpr int kMaxRegRelief = 2;
 // Whether plain products may split a contraction over workgroups (thread-local;
-// off while a plan is generated again that the split's scratch would keep out
-// of the static scratch of allocation-free execution).
+// off while kernels are generated for allocation-free execution of a plan that
+// the splits' scratch would keep out of the static one).
 void set_workgroup_splits(bool on);
 bool workgroup_splits();
 // The fissioned Mish pattern rooted at `node` (a product); returns its input or -1.

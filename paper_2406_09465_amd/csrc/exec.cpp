@@ -66,18 +66,20 @@ static void generate_kernels(Plan& p) {
 }
 
 // The splits' scratch and counters must not keep a plan out of allocation-free
-// execution: a plan that only fits the static scratch without them has none
-// (one that splits nothing is generated once, whatever it needs).
+// execution: a plan that only fits the static scratch without them has kernels
+// without them for it.
 void generate_plan(Plan& p) {
   if (!p.ck.empty()) return;
   generate_kernels(p);
   const bool split = std::any_of(p.ck.begin(), p.ck.end(), [](const CompiledKernel& c) { return c.gen.wg_split; });
   if (!split || fits_static_scratch(p)) return;
-  p.wg_splits = false;
-  generate_kernels(p);
-  if (fits_static_scratch(p)) return;
-  p.wg_splits = true;
-  generate_kernels(p);
+  auto q = std::make_unique<Plan>();
+  q->g = p.g;
+  q->kernels = p.kernels;
+  q->name_prefix = p.name_prefix;
+  q->wg_splits = false;
+  generate_kernels(*q);
+  if (fits_static_scratch(*q)) p.unsplit = std::move(q);
 }
 
 // Kernels are compiled on the calling thread: hipRTC runs in a link namespace
@@ -137,6 +139,7 @@ void compile_plan(Plan& p) {
     }
   }
   if (regenerated) plan_workspace(p);  // a regenerated kernel may take other scratch arguments
+  if (p.unsplit) compile_plan(*p.unsplit);
   p.compiled = true;
 }
 
@@ -152,13 +155,17 @@ static void unload(Plan& p) {
   p.loaded = false;
 }
 
-void destroy_plan_device(Plan& p) { unload(p); }
+void destroy_plan_device(Plan& p) {
+  unload(p);
+  if (p.unsplit) unload(*p.unsplit);
+}
 
 void load_plan(Plan& p) {
   compile_plan(p);
   int dev = 0;
   HIPCHECK(hipGetDevice(&dev));
   if (p.loaded && p.counter_device == dev) return;
+  if (p.unsplit) load_plan(*p.unsplit);
   unload(p);
   for (auto& ck : p.ck) {
     hipModule_t m;
@@ -270,6 +277,7 @@ void execute_plan_noalloc(Plan& p, const void* const* inputs, void* const* outpu
   if (dev != p.counter_device)
     fail(KORCH_E_STATE, "plan is loaded on device " + std::to_string(p.counter_device) + ", not on the current device " +
                             std::to_string(dev) + ": call korch_plan_load again");
+  if (p.unsplit) return execute_plan_noalloc(*p.unsplit, inputs, outputs, stream);
   char* base = (char*)static_scratch_address(dev);
   if (!base) fail(KORCH_E_STATE, "static scratch not set up on this device: call korch_plan_load");
   const size_t ws_cap = static_scratch_bytes() - kStaticCounterBytes;
@@ -412,13 +420,13 @@ float profile_candidate(const Graph& g, const KernelDesc& kd, int warmup, int re
       delete[] ev;
     }
     for (void* q : bufs) hipFree(q);
-    unload(p);
+    destroy_plan_device(p);
     throw;
   }
   for (int r = 0; r < 2 * reps; ++r) hipEventDestroy(ev[r]);
   delete[] ev;
   for (void* q : bufs) hipFree(q);
-  unload(p);
+  destroy_plan_device(p);
   if (times.empty()) return 0.0f;
   std::sort(times.begin(), times.end());
   return times[times.size() / 2];

@@ -2,6 +2,7 @@
 #pragma once
 
 #include <map>
+#include <memory>
 #include <string>
 #include <vector>
 
@@ -40,6 +41,9 @@ struct Plan {
   std::map<int, size_t> ws_offset;  // workspace-resident materialized node -> offset
   std::string name_prefix = "korch_k";  // kernel symbols: <prefix><index>_<family>
   bool wg_splits = true;  // products may split a contraction over workgroups
+  // The plan's kernels without such splits, for allocation-free execution,
+  // where the plan fits the static scratch only without their partial sums.
+  std::unique_ptr<Plan> unsplit;
 };
 
 // Checks a plan against Definitions 1 and 3 and the ordered dependency /

@@ -142,19 +142,57 @@ def test_phased_epilogue_that_spills_takes_smaller_tiles():
     assert p.kernel_launch(0)[0][0] == 16384 // 256 * 4096 // 128
 
 
-def test_workgroup_splits_keep_plans_allocation_free():
-    """A long product of few tiles splits its contraction over workgroups; a
-    plan whose tensors would fill the static scratch of allocation-free
-    execution together with the split's partial sums has no split."""
+# Plans whose tensors fill the static scratch of allocation-free execution, but
+# not together with a split's partial sums: the hidden activation alone is 512 x
+# 32000 fp16 = 32,768,000 of 33,488,896 bytes.
+NEAR_LIMIT = dict(m=512, d=192, h=32000)
+
+
+def test_workgroup_splits_keep_callers_workspace():
+    """A long product of few tiles splits its contraction over workgroups, also
+    where the plan with the split's partial sums is past the static scratch (the
+    caller brings the workspace)."""
     from paper_2406_09465_amd import graphs
     static_ws = 33488896
     p = graphs.build("mlp", m=64, d=768, h=3072).plan("layered")
     assert "split_" in p.kernel_source(2) and p.workspace_bytes() <= static_ws
-    h = 32000  # the hidden activation alone: 512 x 32000 fp16 = 32,768,000 bytes
-    p = graphs.build("mlp", m=512, d=192, h=h).plan("layered")
-    assert "split_" not in p.kernel_source(2) and p.workspace_bytes() <= static_ws
-    p = graphs.build("mlp", m=512, d=192, h=40960).plan("layered")  # too large either way
-    assert "split_" in p.kernel_source(2) and p.workspace_bytes() > static_ws
+    for sizes in (NEAR_LIMIT, dict(m=512, d=192, h=40960)):
+        p = graphs.build("mlp", **sizes).plan("layered")
+        assert "split_" in p.kernel_source(2) and p.workspace_bytes() > static_ws
+
+
+@pytest.mark.gpu
+def test_workgroup_splits_keep_plans_allocation_free():
+    """Allocation-free execution of a plan that fits the static scratch only
+    without splits runs it without them; one that does not fit either way is
+    refused."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2406_09465_amd import graphs
+    from paper_2406_09465_amd._abi import KorchError, pointer_array
+    from paper_2406_09465_amd.runner import PlanRunner
+    from synthetic import workloads as W
+    for sizes in (NEAR_LIMIT, dict(m=512, d=192, h=40960)):
+        print(f"\n[case] near the static scratch {sizes}", flush=True)
+        r = PlanRunner(graphs.build("mlp", **sizes), "layered")
+        r.set_inputs(W.inputs("mlp", **sizes))
+        r.launch()
+        torch.cuda.synchronize()
+        ref = r.outs[0].double()
+        out = torch.zeros_like(r.outs[0])
+        args = (pointer_array([t.data_ptr() for t in r.ins]), pointer_array([out.data_ptr()]), torch.cuda.current_stream().cuda_stream)
+        if sizes is not NEAR_LIMIT:
+            with pytest.raises(KorchError) as e:
+                r.plan.execute_noalloc(*args)
+            assert e.value.code == -22
+            continue
+        for _ in range(3):
+            out.zero_()
+            r.plan.execute_noalloc(*args)
+            torch.cuda.synchronize()
+            # the same products in another order of fp32 sums, rounded to fp16 once
+            err = (out.double() - ref).abs()
+            assert float((err - 2.0 ** -10 * ref.abs()).max()) <= 2.0 ** -10 * float(ref.abs().mean())
 
 
 def test_phased_selection():
