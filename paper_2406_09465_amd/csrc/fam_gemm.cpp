@@ -384,7 +384,8 @@ void choose_tiles(GemmSpec& sp, bool split) {
   // profiler); ignored unless it is consistent.
   if (const char* e = getenv("KORCH_GEMM_CFG")) {
     int bm, bn, bk, wm, wn;
-    if (!split && sscanf(e, "%d,%d,%d,%d,%d", &bm, &bn, &bk, &wm, &wn) == 5 && (wm * wn == 4 || wm * wn == 8) &&
+    if (!split && sscanf(e, "%d,%d,%d,%d,%d", &bm, &bn, &bk, &wm, &wn) == 5 && bm > 0 && bm <= 512 && bn > 0 && bn <= 512 &&
+        wm > 0 && wm <= 8 && wn > 0 && wn <= 8 && bk <= 256 && (wm * wn == 4 || wm * wn == 8) &&
         bm % (16 * wm) == 0 && bn % (16 * wn) == 0 && bk % sp.kstep == 0 && bk >= sp.kstep &&
         (sp.mms.size() == 1 || bn >= sp.Ntot)) {
       sp.BM = bm;

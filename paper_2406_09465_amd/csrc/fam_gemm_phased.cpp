@@ -85,6 +85,9 @@ static bool phased_tiles(GemmSpec& sp, bool reads_rows) {
   if (const char* e = getenv("KORCH_GEMM_PHASED")) {
     int bm, bn, wm, wn, kg, st, bk, ks = 1;
     if (sscanf(e, "%d,%d,%d,%d,%d,%d,%d,%d", &bm, &bn, &wm, &wn, &kg, &bk, &st, &ks) < 7) return false;
+    if (bm < 16 || bm > 512 || bn < 16 || bn > 512 || wm < 1 || wm > 8 || wn < 1 || wn > 8 || kg < 1 || kg > 8 || bk < 16 || bk > 64 || st < 2 ||
+        st > 12 || ks < 1 || ks > 256)
+      return false;
     sp.BM = bm, sp.BN = bn, sp.WM = wm, sp.WN = wn, sp.KG = kg, sp.PST = st, sp.BK = bk, sp.KS = ks;
     return true;
   }
@@ -332,7 +335,9 @@ bool plan_phased(const KInfo& ki, GemmSpec& sp, bool split_halves) {
   t.bt = bt;
   if (!phased_tiles(t, epilogue_reads_rows(ki, t))) return false;
   if (t.conv && t.Cin % t.BK) t.BK /= 2, t.PST = std::min(12, 2 * t.PST);  // the same LDS in twice the stages
-  if (t.KS < 1 || t.KS * t.KG > (t.K + t.BK - 1) / t.BK) t.KS = 1;
+  if (t.KS * t.KG > (t.K + t.BK - 1) / t.BK) t.KS = 1;
+  // (partial tiles are addressed with 32-bit byte offsets)
+  if ((double)((t.M + t.BM - 1) / t.BM * ((t.N + t.BN - 1) / t.BN) * t.batch) * t.KS * t.BM * t.BN * 4 >= 2147483648.0) t.KS = 1;
   // no stages that the contraction does not fill: short ones are bound by their
   // first loads and stores, which more workgroups per compute unit overlap
   if (!getenv("KORCH_GEMM_PHASED"))
@@ -342,7 +347,7 @@ bool plan_phased(const KInfo& ki, GemmSpec& sp, bool split_halves) {
   // with register staging does: the results are the same to the bit (wave tiles
   // of up to 16 blocks, which leave registers for the second set of sums).
   t.KSEQ = t.KG == 1 && t.KS == 1 && split_halves && t.BM / t.WM * (t.BN / t.WN) <= 16 * 256 ? 2 : 1;
-  if (t.WM < 1 || t.WN < 1 || t.KG < 1 || t.BM % (16 * t.WM) || t.BN % (16 * t.WN)) return false;
+  if (t.BM % (16 * t.WM) || t.BN % (16 * t.WN)) return false;
   const int gw = t.WM * t.WN;  // waves per group
   t.NT = 64 * gw * t.KG;
   if (t.NT != 256 && t.NT != 512) return false;
@@ -350,7 +355,6 @@ bool plan_phased(const KInfo& ki, GemmSpec& sp, bool split_halves) {
   if ((t.BM * t.BK / (64 * CE)) % gw || t.BN * t.BK % (64 * CE)) return false;  // whole blocks, the left operand's shared evenly
   t.WTM = t.BM / t.WM, t.WTN = t.BN / t.WN;
   t.FM = t.WTM / 16, t.FN = t.WTN / 16;
-  if (t.PST < 2 || t.PST > 12) return false;
   t.LDC = t.BN + 4;
   if (CE == 8 && bt < 0 && !dma_b_swizzle(t.BN / 8, t.dx0, t.dx1, t.dx3)) return false;
   t.acc_t = false;

@@ -195,6 +195,34 @@ def test_workgroup_splits_keep_plans_allocation_free():
             assert float((err - 2.0 ** -10 * ref.abs()).max()) <= 2.0 ** -10 * float(ref.abs().mean())
 
 
+@pytest.mark.parametrize("switch", [
+    "KORCH_GEMM_PHASED=128,128,0,2,1,64,2", "KORCH_GEMM_PHASED=128,128,2,2,1,0,2", "KORCH_GEMM_PHASED=0,128,2,2,1,64,2",
+    "KORCH_GEMM_PHASED=128,-128,2,2,1,64,2", "KORCH_GEMM_PHASED=128,128,2,2,0,64,2", "KORCH_GEMM_PHASED=128,128,-2,-2,1,64,2",
+    "KORCH_GEMM_PHASED=128,128,2,2,1,64,1000000000", "KORCH_GEMM_PHASED=1073741824,128,2,2,1,64,2",
+    "KORCH_GEMM_CFG=0,128,32,2,2", "KORCH_GEMM_CFG=128,0,32,2,2", "KORCH_GEMM_CFG=128,128,32,-2,-2", "KORCH_GEMM_CFG=-128,128,32,2,2",
+    "KORCH_GEMM_CFG=128,128,0,2,2"])
+def test_inconsistent_tile_switches_are_ignored(switch):
+    """In a process of its own (the first forms ended it with a division by zero)."""
+    import os
+    import subprocess
+    import sys
+    code = """
+from paper_2406_09465_amd._abi import Graph, Plan
+g = Graph()
+a, b = g.input("f16", (700, 1032)), g.input("f16", (1032, 520))
+c = g.op("matmul", [a, b], "f16")
+g.output(c)
+g.finalize()
+p = Plan(g, [([c], [c])])
+grid, block, lds = p.kernel_launch(0)
+assert min(grid + block) > 0 and block[0] in (256, 512) and lds <= 160 * 1024
+"""
+    var, val = switch.split("=")
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", code], env={**os.environ, var: val}, cwd=root, capture_output=True, text=True)
+    assert r.returncode == 0, (r.returncode, r.stderr[-300:])
+
+
 def test_phased_selection():
     """Plain products take the path; rows that do not start on dwords and small
     short 16-bit products do not."""
