@@ -274,7 +274,7 @@ bool plan_phased(const KInfo& ki, GemmSpec& sp, bool split_halves) {
   // the switches of the older staging paths ask for those paths
   for (const char* n : {"KORCH_GEMM_CFG", "KORCH_GEMM_NS", "KORCH_GEMM_NO_KSPLIT", "KORCH_GEMM_DMA", "KORCH_GEMM_DMA8",
                         "KORCH_GEMM_DMA_KSPLIT", "KORCH_GEMM_DMA_2STAGE", "KORCH_GEMM_DMA_A3", "KORCH_GEMM_DMA_STAGES",
-                        "KORCH_GEMM_SPLIT_STEPS"})
+                        "KORCH_GEMM_SPLIT_STEPS", "KORCH_GEMM_SCHED", "KORCH_GEMM_FULL_CTILE", "KORCH_LDS_BANK_SHIFT"})
     if (env_set(n)) return false;
   if (reg_relief() >= 2) return false;
   if (sp.lnf || sp.mms.size() != 1 || sp.Bs.size() != 1 || !sp.side.empty() || !sp.rowred.empty()) return false;

@@ -266,7 +266,7 @@ GenKernel gen_splitk(const KInfo& ki, int index) {
   // (16-bit outputs of up to 32 columns keep the narrow tiles below unless their
   // contraction's rows are not 16-byte chunks: 2000 x 24 x 2000 takes 4.9 us here,
   // 5.6 in 64-column tiles; 1478 x 16 x 1478 5.9 and 5.1)
-  if ((sp.mtype == KORCH_F32 || sp.N > 32 || sp.K % 8) && plan_phased(ki, sp, false)) {
+  if (!getenv("KORCH_SPLITK_WGS") && (sp.mtype == KORCH_F32 || sp.N > 32 || sp.K % 8) && plan_phased(ki, sp, false)) {
     GenKernel ph = gen_gemm_phased(ki, sp, index, "splitk");
     ph.family = KORCH_FAM_SPLITK;
     return ph;

@@ -195,6 +195,22 @@ def test_workgroup_splits_keep_plans_allocation_free():
             assert float((err - 2.0 ** -10 * ref.abs()).max()) <= 2.0 ** -10 * float(ref.abs().mean())
 
 
+@pytest.mark.parametrize("switch,product", [("KORCH_GEMM_SCHED=0", (1024, 1024, 1024)), ("KORCH_GEMM_FULL_CTILE=1", (1024, 1024, 1024)),
+                                            ("KORCH_LDS_BANK_SHIFT=0", (1024, 1024, 1024)), ("KORCH_SPLITK_WGS=32", (64, 64, 8192))])
+def test_switches_of_the_older_loops_take_them(switch, product, monkeypatch):
+    """Ablation switches that only the older loops have act on products that run
+    the phased loop without them."""
+    from paper_2406_09465_amd._abi import Plan
+    w, kernels = _graph(*product, "f16", "")
+    assert "offen lds" in Plan(w.graph, kernels).kernel_source(0)
+    monkeypatch.setenv(*switch.split("="))
+    p = Plan(w.graph, kernels)
+    assert "offen lds" not in p.kernel_source(0)
+    if "WGS" in switch:
+        (grid, _, _) = p.kernel_launch(0)
+        assert grid[0] * grid[1] * grid[2] <= 32
+
+
 @pytest.mark.parametrize("switch", [
     "KORCH_GEMM_PHASED=128,128,0,2,1,64,2", "KORCH_GEMM_PHASED=128,128,2,2,1,0,2", "KORCH_GEMM_PHASED=0,128,2,2,1,64,2",
     "KORCH_GEMM_PHASED=128,-128,2,2,1,64,2", "KORCH_GEMM_PHASED=128,128,2,2,0,64,2", "KORCH_GEMM_PHASED=128,128,-2,-2,1,64,2",
