@@ -269,6 +269,13 @@ static bool epilogue_reads_rows(const KInfo& ki, const GemmSpec& sp) {
   return false;
 }
 
+// The first k-tile whose lines are touched ahead (those before are loaded by the
+// time a touch is back), and the cache lines from there on.
+constexpr int kTouchFrom = 16;
+static int64_t touch_lines(const GemmSpec& sp) {
+  return ((sp.K - (int64_t)kTouchFrom * sp.BK) * sp.N * dtype_bytes(sp.mtype) + 127) / 128;
+}
+
 bool plan_phased(const KInfo& ki, GemmSpec& sp, bool split_halves) {
   sp.KG = 0;
   // the switches of the older staging paths ask for those paths
@@ -366,6 +373,19 @@ bool plan_phased(const KInfo& ki, GemmSpec& sp, bool split_halves) {
     t.OSB = t.BM * t.OSP * 2;
   }
   if (phased_smem(t) + (t.KS > 1 ? 16 : 0) > 160 * 1024) return false;
+  // Every workgroup of a long contraction meets the weights' next k-tile at the
+  // same time, and after a flush each waits for HBM: the MLP block's second
+  // product (4096 x 768 x 3072) took 29.1 us against 24.4 warm, the k-split
+  // kernel before it 28.4.  So the workgroups first touch the later k-tiles
+  // together, each a share of their cache lines: 25.6 us (the block 54.8 after a
+  // flush, 58.5 without; 49.3 warm either way).  Fewer rows than this pay for the
+  // touches when warm (1193 x 832 x 3328: the block 28.7 and 28.2 us, after a flush
+  // 34.3 and 36.5); fp32 products are too slow to wait for HBM.
+  t.touch = 0;
+  if (CE == 8 && !t.conv && t.batch == 1 && t.KS == 1 && t.KG == 1 && t.M >= 2560 && t.K >= 2 * kTouchFrom * t.BK) {
+    const int64_t wgs = (t.M + t.BM - 1) / t.BM * ((t.N + t.BN - 1) / t.BN), per = (touch_lines(t) + wgs - 1) / wgs;
+    if (wgs >= 128 && wgs <= 512 && per <= t.NT) t.touch = (int)per;
+  }
   sp = t;
   return true;
 }
@@ -626,6 +646,12 @@ static std::string phased_mainloop(const GemmSpec& sp, int64_t KTG, bool exact) 
   const int64_t KS = exact ? KTG : KTG - 1;  // k-tiles that every group has
   for (int t = 0; t < NST && t < KTG; ++t)
     s << "  " << (t < KS ? "" : "if (" + std::to_string(t) + " < nkt_) ") << "load_(kt0 + " << t << ", " << t << ");\n";
+  if (sp.touch)
+    // (plan_phased; behind the loads of the first tiles, so that a wait for the
+    // oldest loads does not wait for this one)
+    s << "  unsigned touch_ = 0;\n  if (tid < " << sp.touch << " && (i64)wg * " << sp.touch << " + tid < " << touch_lines(sp)
+      << "LL) touch_ = *(const unsigned*)((const char*)pB_ + " << (int64_t)kTouchFrom * sp.BK * sp.N * eb << "LL + ((i64)wg * " << sp.touch
+      << " + tid) * 128);\n";
   // tile 0 landed; the tiles after it may be in flight
   s << wait(KS >= NST ? NST - 1 : 0) << "  __syncthreads();\n";
   if (ragged && last == 0) s << trim(0);
@@ -646,6 +672,7 @@ static std::string phased_mainloop(const GemmSpec& sp, int64_t KTG, bool exact) 
   if (sp.KSEQ > 1)
     s << "#pragma unroll\n  for (int i = 0; i < " << sp.FM << "; ++i)\n#pragma unroll\n  for (int n = 0; n < " << sp.FN
       << "; ++n) acc[i][n] = acc0_[i][n] + acc[i][n];\n";
+  if (sp.touch) s << "  asm volatile(\"\" :: \"v\"(touch_));\n";
   s << "  __syncthreads();\n";
   return s.str();
 }

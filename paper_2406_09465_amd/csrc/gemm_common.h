@@ -74,6 +74,7 @@ struct GemmSpec {
   int PST = 2;   // its stages of each operand
   int KS = 1;    // workgroups that share a tile's contraction
   int KSEQ = 1;  // parts of the contraction summed one after another, then added
+  int touch = 0; // cache lines of the right operand that each workgroup touches first (0: none)
   // LayerNorm folded into the product (see detect_ln_fold): the left operand
   // is LN(X) = (X - mu) r gamma + beta over X's last axis; the kernel stages X,
   // multiplies X gamma by the right operand W, accumulates each row's sum and

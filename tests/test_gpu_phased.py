@@ -345,6 +345,46 @@ def test_phased_tile_rule(product, tile):
         assert (got[0], got[1], got[2] // eb, "split_ =" in src) == tile
 
 
+# Products whose workgroups first touch the later part of the right operand: the
+# MLP block's second product, ragged rows, columns and contraction, a transposed
+# operand, the shortest contraction and the fewest rows; and one row less.
+TOUCHES = [(4096, 768, 3072, "f16", False), (2600, 770, 2122, "bf16", False), (2997, 744, 2050, "f16", True), (2560, 832, 2048, "bf16", False)]
+
+
+@pytest.mark.parametrize("product", TOUCHES, ids=lambda c: "x".join(map(str, c)))
+def test_phased_touch_stays_inside_the_operand(product):
+    """The touched dwords, over every workgroup and thread, lie in the right
+    operand, and cover each of its cache lines from the first touched one on."""
+    import re
+    from paper_2406_09465_amd._abi import Plan
+    m, n, k, dtype, bt = product
+    w, kernels = _graph(m, n, k, dtype, "residual", bt=bt)
+    p = Plan(w.graph, kernels)
+    src, (grid, block, _) = p.kernel_source(0), p.kernel_launch(0)
+    per, per2, lines, first, per3 = map(int, re.search(
+        r"if \(tid < (\d+) && \(i64\)wg \* (\d+) \+ tid < (\d+)LL\) touch_ = \*\(const unsigned\*\)\(\(const char\*\)pB_ \+ (\d+)LL \+ "
+        r"\(\(i64\)wg \* (\d+) \+ tid\) \* 128\);", src).groups())
+    assert per == per2 == per3 <= block[0] and grid[0] * per >= lines
+    assert first % 4 == 0 and first + (lines - 1) * 128 + 4 <= 2 * n * k <= first + lines * 128
+    w, kernels = _graph(2559, n, k, dtype, "residual", bt=bt)
+    assert "touch_" not in Plan(w.graph, kernels).kernel_source(0)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("product", TOUCHES, ids=lambda c: "x".join(map(str, c)))
+def test_phased_touch_products(product):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    m, n, k, dtype, bt = product
+    print(f"\n[case] phased touch {product}", flush=True)
+    r, x = _run(m, n, k, dtype, "residual", seed=k, bt=bt)
+    assert "touch_" in r.plan.kernel_source(0)
+    full, r.outs = r.outs, [r.outs[0][::23]]
+    _check(r, {nm: v[::23] if nm in ("A", "R") else v for nm, v in x.items()}, k, dtype)
+    r.outs = full
+    _repeat(r, f"touch {product}")
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("product", [c for c, _ in CHOICES], ids=lambda c: "x".join(map(str, c)))
 def test_phased_tile_rule_products(product):
