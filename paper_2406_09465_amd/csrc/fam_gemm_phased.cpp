@@ -96,6 +96,13 @@ static bool phased_tiles(GemmSpec& sp, bool reads_rows) {
     double t1, tc, ov;
   };
   double best = 1e300;
+  // A convolution whose channels end half a k-tile short has k-tiles of half the
+  // size (plan_phased), of which a tile's left rows must still be a whole number
+  // of 1 KiB blocks for every wave.
+  auto stages = [&](const Shape_& h, int bk) {
+    if (sp.conv && sp.Cin % bk) bk /= 2;
+    return h.bm * bk * dtype_bytes(sp.mtype) % (1024 * h.wm * h.wn) == 0;
+  };
   if (sp.mtype == KORCH_F32) {
     // fp32 products are bound by their MFMAs (16x16x4: a quarter of a 16-bit
     // k-step's products in twice the clocks), so what a tile costs is its area
@@ -115,6 +122,7 @@ static bool phased_tiles(GemmSpec& sp, bool reads_rows) {
     };
     const double KT = (double)((sp.K + 31) / 32);
     for (const Shape_& h : f32s) {
+      if (!stages(h, 32)) continue;
       const int64_t tiles = (sp.M + h.bm - 1) / h.bm * ((sp.N + h.bn - 1) / h.bn) * sp.batch, n = (tiles + 255) / 256;
       // (over many tiles of a short contraction 32 x 32 ones read the operands too often where 64 columns are
       // not padding: 1687 x 872 x 48, batch of 8, 37.6 us after a flush, 32 x 64 34.1)
@@ -199,6 +207,7 @@ static bool phased_tiles(GemmSpec& sp, bool reads_rows) {
     // 16384 x 4096 x 1024 with it takes 203 us in 256 x 128 tiles, 247 with
     // 128-row tiles staged through registers)
     if (h.bm * h.bn == 256 * 256 && reg_relief() >= 1) continue;
+    if (!stages(h, 64)) continue;
     const int64_t tiles = (sp.M + h.bm - 1) / h.bm * ((sp.N + h.bn - 1) / h.bn) * sp.batch;
     for (int ks = 1; ks <= 16; ++ks) {
       if (ks > 1 && !splits_fit(h.bm, h.bn, tiles, ks, h.kg, KT)) break;

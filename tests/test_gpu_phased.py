@@ -436,6 +436,53 @@ def test_phased_nonfinite_rows_stay_apart():
 # smaller than a tile, more workgroups than pixels, a per-channel epilogue.
 CONVS = [("f16", 52, 52, 128, 256, 3), ("bf16", 9, 7, 256, 48, 5), ("f16", 33, 130, 96, 256, 3), ("f32", 31, 17, 64, 40, 3),
          ("bf16", 64, 64, 192, 96, 1), ("f32", 20, 20, 32, 256, 5), ("f16", 100, 100, 160, 128, 3)]
+# Channels that end half a k-tile short on small maps, whose 32-row tiles have
+# fewer blocks of half a k-tile than waves.
+HALF_CONVS = [("f16", 14, 14, 96, 64, 3), ("f16", 20, 20, 160, 64, 3), ("bf16", 26, 26, 96, 128, 3), ("f16", 52, 52, 96, 128, 3),
+              ("bf16", 57, 23, 96, 256, 3), ("f16", 40, 40, 96, 256, 5), ("f32", 40, 40, 48, 128, 3), ("f32", 13, 13, 80, 64, 3)]
+CONVS += HALF_CONVS
+
+
+@pytest.mark.parametrize("case", HALF_CONVS, ids=lambda c: "x".join(map(str, c)))
+def test_phased_convolution_of_half_k_tiles(case):
+    from paper_2406_09465_amd import graphs
+    dtype, hh, ww, cin, cout, k = case
+    assert "offen lds" in graphs.build("conv", dtype=dtype, hh=hh, ww=ww, cin=cin, cout=cout, k=k).plan("fused").kernel_source(0)
+
+
+# Strides and paddings other than the workload's (1 and k / 2).
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", [("f16", 30, 41, 64, 96, 3, 2, 1), ("bf16", 30, 41, 64, 96, 3, 2, 0), ("f16", 25, 25, 96, 64, 3, 1, 0),
+                                  ("f32", 19, 33, 64, 40, 3, 2, 1), ("f16", 28, 27, 128, 72, 1, 2, 0), ("bf16", 23, 31, 96, 128, 5, 3, 2),
+                                  ("f16", 11, 40, 64, 64, 3, 1, 3)], ids=lambda c: "x".join(map(str, c)))
+def test_phased_convolution_strides(case):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2406_09465_amd._abi import Graph
+    from paper_2406_09465_amd.graphs import Workload
+    from paper_2406_09465_amd.runner import TORCH_DTYPE, PlanRunner
+    dtype, hh, ww, cin, cout, k, stride, pad = case
+    print(f"\n[case] phased conv strides {case}", flush=True)
+    g = Graph()
+    ids = {"X": g.input(dtype, (hh, ww, cin)), "W": g.input(dtype, (k, k, cin, cout)), "b": g.input(dtype, (cout,))}
+    ids["C"] = g.op("conv2d", [ids["X"], ids["W"]], dtype, stride=stride, pad=pad)
+    ids["out"] = g.op("add", [ids["C"], ids["b"]], dtype)
+    g.output(ids["out"])
+    g.finalize()
+    r = PlanRunner(Workload("conv", dtype, g, ids, ["X", "W", "b"], ["out"]), kernels=[([ids["C"], ids["out"]], [ids["out"]])])
+    assert "offen lds" in r.plan.kernel_source(0)
+    gen = torch.Generator(device="cuda").manual_seed(hh + cin)
+    r.ins = [torch.randn(s, generator=gen, device="cuda").to(TORCH_DTYPE[dtype]) for s in ((hh, ww, cin), (k, k, cin, cout), (cout,))]
+    r.bind()
+    r.launch_bound()
+    torch.cuda.synchronize()
+    x, w, b = (t.double().cpu() for t in r.ins)
+    conv = lambda u, v: torch.nn.functional.conv2d(u.permute(2, 0, 1)[None], v.permute(3, 2, 0, 1), stride=stride, padding=pad)[0].permute(1, 2, 0)
+    ref, mag = conv(x, w) + b, conv(x.abs(), w.abs()) + b.abs()
+    eps = {"f16": 2.0 ** -11, "bf16": 2.0 ** -8, "f32": 2.0 ** -24}[dtype]
+    bound = eps * ref.abs() * 1.01 + (k * k * cin + 1) * 2.0 ** -24 * mag + 2.0 ** -24
+    err = (r.outs[0].double().cpu() - ref).abs()
+    assert not bool((err > bound).any()), f"worst {float((err / bound).max()):.2f}"
 
 
 @pytest.mark.gpu
