@@ -724,31 +724,35 @@ static GenKernel gen_colmoments(const KInfo& ki, int index, const Moments& mo) {
   // Welford over this thread's rows (one count for its VB columns)
   s << "  float cn_ = 0.0f, mu_[" << VB << "], m2_[" << VB << "];\n";
   s << "#pragma unroll\n  for (int e = 0; e < " << VB << "; ++e) mu_[e] = 0.0f, m2_[e] = 0.0f;\n";
-  auto rows = [&](bool full) {
+  // one row into a thread's mean and M2; `guard`: the row may not exist (ok_)
+  auto row = [&](bool guard) {
+    s << pe.pre.str() << "    " << (guard ? "if (ok_) " : "") << "cn_ += 1.0f;\n    const float inv_ = " << (guard ? "ok_ ? " : "")
+      << "__builtin_amdgcn_rcpf(cn_)" << (guard ? " : 0.0f" : "") << ";\n";
+    s << "#pragma unroll\n    for (int e = 0; e < " << VB << "; ++e) {\n" << pe.body.str() << "      const float x_ = " << xv
+      << ";\n      const float d_ = " << (guard ? "ok_ ? x_ - mu_[e] : 0.0f" : "x_ - mu_[e]")
+      << ";\n      mu_[e] += d_ * inv_;\n      m2_[e] += d_ * (x_ - mu_[e]);\n    }\n  }\n";
+  };
+  auto batches = [&](bool full) {
     if (NBAT > 1) s << "#pragma unroll 1\n  for (int bt_ = 0; bt_ < " << NBAT << "; ++bt_)\n";
     s << "#pragma unroll\n  for (int it_ = 0; it_ < " << U << "; ++it_) {\n    const i64 lr_ = l0 + ly + (i64)("
       << (NBAT > 1 ? "bt_ * " + std::to_string(U) + " + " : std::string()) << "it_) * " << LY << ";\n";
-    if (full)
-      s << "    const i64 l = lr_;\n" << pe.pre.str() << "    cn_ += 1.0f;\n    const float inv_ = __builtin_amdgcn_rcpf(cn_);\n";
-    else
-      s << "    const bool ok_ = lr_ < l1;\n    const i64 l = ok_ ? lr_ : l1 - 1;\n" << pe.pre.str()
-        << "    if (ok_) cn_ += 1.0f;\n    const float inv_ = ok_ ? __builtin_amdgcn_rcpf(cn_) : 0.0f;\n";
-    s << "#pragma unroll\n    for (int e = 0; e < " << VB << "; ++e) {\n" << pe.body.str();
-    s << "      const float x_ = " << xv << ";\n";
-    s << "      const float d_ = " << (full ? "x_ - mu_[e]" : "ok_ ? x_ - mu_[e] : 0.0f")
-      << ";\n      mu_[e] += d_ * inv_;\n      m2_[e] += d_ * (x_ - mu_[e]);\n    }\n  }\n";
+    s << (full ? "    const i64 l = lr_;\n" : "    const bool ok_ = lr_ < l1;\n    const i64 l = ok_ ? lr_ : l1 - 1;\n");
+    row(!full);
   };
   const bool last_partial = Lr % chunk != 0;
   if (plain_loop) {
-    s << row_loop(chunk, Lr, LY) << pe.pre.str() << "    cn_ += 1.0f;\n    const float inv_ = __builtin_amdgcn_rcpf(cn_);\n";
-    s << "#pragma unroll\n    for (int e = 0; e < " << VB << "; ++e) {\n" << pe.body.str() << "      const float x_ = " << xv
-      << ";\n      const float d_ = x_ - mu_[e];\n      mu_[e] += d_ * inv_;\n      m2_[e] += d_ * (x_ - mu_[e]);\n    }\n  }\n";
+    s << row_loop(chunk, Lr, LY);
+    row(false);
+  } else if (!rows_full) {
+    batches(false);
+  } else if (!last_partial) {
+    batches(true);
   } else {
-  if (rows_full && last_partial) s << "  if (l0 + " << chunk << " <= " << Lr << "LL) {\n";
-  if (rows_full) rows(true);
-  if (rows_full && last_partial) s << "  } else {\n";
-  if (!rows_full || last_partial) rows(false);
-  if (rows_full && last_partial) s << "  }\n";
+    s << "  if (l0 + " << chunk << " <= " << Lr << "LL) {\n";
+    batches(true);
+    s << "  } else {\n";
+    batches(false);
+    s << "  }\n";
   }
   // merge (na, ma, qa) (the lower) with (nb, mb, qb): f = nb / n, w = na nb / n
   s << "  const int wv_ = tid >> 6, lane_ = tid & 63;\n";
