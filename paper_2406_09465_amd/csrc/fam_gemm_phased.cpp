@@ -1,14 +1,16 @@
-// Phased main loop of the GEMM family: plain 16-bit products staged direct to
-// LDS, one barrier per k-tile with the matrix cores busy across it.
+// Phased main loop of the GEMM, conv and split-K families: products and implicit
+// convolutions of plain 16-bit or fp32 operands staged direct to LDS, one barrier
+// per k-tile with the matrix cores busy across it, long contractions split over
+// workgroups.
 //
 // What bounds it: of a 16384 x 1024 x 4096 product with 256 x 256 tiles (109 us,
 // 1.26 PFLOP/s; the 128 x 128 tiles staged as before took 195 us) the loads
-// alone take 101 us and the products with their LDS reads alone 72, so the tile
-// is as large as registers and LDS allow and the loads run under the products;
-// the L2 misses are the compulsory ones, and each compute unit's L1 is refused
-// requests 56 % of the time for having about 80 in flight.  LDS reads cost
-// nothing measurable: two wave rows of 128 tile rows each read the right operand,
-// whose transposing reads are the slow ones, only twice.
+// alone took 101 us in a probe and the products with their LDS reads alone 72, so
+// the tile is as large as registers and LDS allow and the loads run under the
+// products; the L2 misses are the compulsory ones, and each compute unit's L1
+// holds 40 to 61 requests of 340 to 390 clocks and refuses more 28 to 37 % of the
+// time.  LDS reads cost nothing measurable: two wave rows of 128 tile rows each
+// read the right operand, whose transposing reads are the slow ones, only twice.
 //
 // A k-tile is NP phases: its k-steps, and the wave's row blocks in pairs.  Phase
 // p multiplies fragments that were read one or two phases before, and the barrier
@@ -62,10 +64,8 @@ static double handoff(int bm, int bn, int ks, int kg, double fill, bool f32) {
 // ov us per round of workgroups for the first loads and the epilogue.  The last,
 // partial round pays for the workgroups it puts on one compute unit.  Large
 // tiles draw the fewest operand bytes per product, which is what bounds a full
-// chip: each compute unit's L1 holds about 80 outstanding 128-byte requests of
-// some 620 clocks (at 256 x 256 it is refused requests 56 % of the time; L2
-// misses are the compulsory ones); small tiles with deep stages cover latency
-// when there are few of them.
+// chip (see above); small tiles with deep stages cover latency when there are few
+// of them.
 //
 // What is not a full chip of cache-resident operands is priced by terms fitted
 // to 2700 16-bit and 800 fp32 kernels (every shape, 1 to 16384 rows, 1 to 16
@@ -307,8 +307,11 @@ bool plan_phased(const KInfo& ki, GemmSpec& sp, bool split_halves) {
   if (sp.K * eb % 4 || (bt < 0 && sp.N * eb % 4)) return false;
   // buffer loads: byte offsets below 2 GiB from a batch's operand
   if ((double)sp.M * sp.K * eb >= 2147483648.0 || (double)sp.K * sp.N * eb >= 2147483648.0) return false;
-  // Products that 192-wide tiles divide into whole rounds keep those tiles and
-  // their own staging (4096 x 3072 x 768 with a GELU: 22.9 us, phased 22.4).
+  // Products for which the older rule takes 192-wide tiles keep them and their
+  // staging: three stages direct to LDS where the tiles divide the problem (4096 x
+  // 3072 x 768 with a GELU: 22.9 us, phased 22.4), through registers elsewhere
+  // (4095 rows, say).  That line is the older rule's, not one of cost; both sides
+  // are measured at that one product only.
   if (!getenv("KORCH_GEMM_PHASED") && sp.BN == 192 && !sp.conv) return false;
   // So do small products of up to four k-tiles whose tiles divide them: there is
   // nothing to pipeline (1024 x 768 x 256: 3.8 us, phased 3.9; 16384 x 64 x 256:
